@@ -44,8 +44,8 @@ def log(msg):
     print(msg, file=sys.stderr, flush=True)
 
 
-KERNEL_SOURCES = ("paper_2509_25840_amd/csrc/kernels.h", "paper_2509_25840_amd/csrc/closure.h",
-                  "paper_2509_25840_amd/csrc/chfpe.hip")
+KERNEL_SOURCES = tuple(f"paper_2509_25840_amd/csrc/{name}" for name in sorted(
+    os.listdir(os.path.join(ROOT, "paper_2509_25840_amd", "csrc"))) if name.endswith((".h", ".hip")))
 
 
 def code_of(text: str) -> str:
@@ -251,8 +251,8 @@ def _kind_of(short: str, grid: int, min_grid: dict):
     targs = [a.strip() for a in short[short.find("<") + 1:short.rfind(">")].split(",")] if "<" in short else []
     if fam == "k_pblock":
         kind = "perturb" if targs[5] == "true" else "pblock_rhs"  # <T, TO, NMAX, RPT, MM, PERTURB, CLOS>
-    elif fam in ("k_pcube", "k_pcube_s"):
-        kind = "perturb" if targs[4] == "true" else "pcube_rhs"  # <T, TO, NB1, SPLIT, PERTURB[, CLOS]>
+    elif fam in ("k_pcube", "k_pcube_s", "k_pwave"):
+        kind = "perturb" if targs[4] == "true" else "pcube_rhs"  # <T, TO, NB1, SPLIT or NVR, PERTURB[, CLOS]>
     elif fam == "k_qpass":
         if int(targs[5]) == 2:        # dX/dq field: second launch of a perturbation
             kind = "perturb_q"
@@ -260,6 +260,8 @@ def _kind_of(short: str, grid: int, min_grid: dict):
             kind = _EPI_KIND[int(targs[4])]
     elif fam == "k_hcube":
         kind = _HEPI_KIND[int(targs[3])]  # <T, NB1, SPLIT, EPI>
+    elif fam == "k_hwave":
+        kind = "hcube_rk4"  # <T, NB, NVR, MM>: the stage update is an argument, one kind for all
     elif fam == "k_hperturb":
         kind = "perturb"
     elif fam == "k_reduce_w0":
@@ -341,7 +343,7 @@ def summarise_counters(args, kern_cmd: str) -> None:
         passes.append(names)
         for r in rows:
             s = _short_name(r["Kernel_Name"])
-            if not s.startswith(("k_pcube", "k_qpass", "k_pblock", "k_hcube")):
+            if not s.startswith(("k_pcube", "k_pwave", "k_qpass", "k_pblock", "k_hcube", "k_hwave")):
                 continue
             key = (s, _grid(r))
             per.setdefault(key, {})

@@ -27,9 +27,10 @@
 
 #include <type_traits>
 
-#include "chfpe.h"
 #include "closure.h"
-#include "kernels.h"
+#include "context.h"
+#include "launch.h"
+#include "small.h"
 
 using namespace chfpe;
 
@@ -38,13 +39,10 @@ namespace {
 thread_local std::string g_setup_error = "no error";
 
 constexpr int kPBlockThreads = 256;  // k_pblock workgroup size (upper bound)
-constexpr int kPBlockRPT = 4;        // rows per k_pblock thread
 constexpr int kQThreadsMax = 512;    // largest k_qpass workgroup
 
 // Kernel kinds for event timing; batched launches (several branch states per
 // launch) are kept apart from single-state ones.
-constexpr int kNumBase = 15;
-constexpr int kNumKinds = 2 * kNumBase;
 enum Kind : int {
   K_PBLOCK = 0,
   K_QACC = 1,
@@ -76,17 +74,6 @@ const char *kKindNames[kNumKinds] = {
 const double kKindPasses[kNumBase] = {2, 3, 3, 4, 4, 4, 0.1, 2, 3, 2, 2, 3, 3, 3, 2};
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
-
-struct Derived {
-  int prec = 0, B = 1;    // precision of branch states; branches per wave
-  bool batched = false;   // 2D responses use the batched branch buffers
-  bool hermite = false;   // Hermite basis in p: P counts Hermite functions, layout [n][k][q]
-  int M = 0, K = 0, ne = 0;
-  int Nq[3] = {0, 0, 0}, Np[3] = {0, 0, 0};  // axes s >= M stay 0
-  int Q = 0, P = 0;
-  long long E, S;  // points per element, values per state
-  std::vector<int> nvec;  // ne * M
-};
 
 // A dispatch's grid size counts work-items in 32 bits: every launch must stay
 // within it (a larger one would wrap and leave tasks unrun).
@@ -129,15 +116,10 @@ PBShape pblock_shape(const Derived &d) {
   return s;
 }
 
-int nmax_bucket(int n) {
-  return n <= 8 ? 8 : n <= 12 ? 12 : n <= 16 ? 16 : n <= 24 ? 24 : n <= 32 ? 32 : 48;
-}
-
 // The p block of k_pcube for two or three modes: p_1 lines (registers) of
 // up to 32 points (three modes) or 48 (two modes), a (p_2, p_3) plane (two
 // modes: a p_2 row) of threads within the workgroup bound, and the LDS copy
 // of the block plus a round's planes within 160 KB (FP64).
-int pcube_n3(const Derived &d) { return d.M == 3 ? d.Np[2] : 1; }
 bool pcube_shape_ok(const Derived &d) {
   if (d.M < 2) return false;
   const int nb1 = nmax_bucket(d.Np[0]);
@@ -291,16 +273,6 @@ bool derive(const chfpe_params *p, Derived &d, std::string &err) {
   return true;
 }
 
-constexpr int kStateBufs = 6;   // FP64: W_eq, U, y, xa, xb, t
-constexpr int kBranchBufs = 4;  // per branch of a wave: y, xa, xb, t
-
-// Workspace layout (byte offsets, 256-aligned).
-struct Layout {
-  size_t F, VpQ, Vp, pm, pg, gA, gB, gC, Cw, wp, sq, sp, up, dn, cc, tc, damp, partial, scal, flag, clos;
-  size_t bufs[kStateBufs];
-  size_t bbufs[kBranchBufs];  // batched branch buffers: y, xa, xb, t (B states each)
-  size_t total;
-};
 constexpr int kPartials = 2048;
 
 Layout layout(const Derived &d) {
@@ -339,35 +311,6 @@ Layout layout(const Derived &d) {
   return L;
 }
 
-struct Launch {
-  PBlock pb{};
-  size_t pb_lds = 0;
-  int pb_threads = 256, pb_nmax = 48;
-  int pb_rpt = 4;  // rows per k_pblock thread (3 where it tiles the 24-row blocks exactly)
-  // strided-axis passes of one stage: qa (three modes only, accumulates into
-  // t) then qf (applies the stage update); qx: the p_1 excitation pass of
-  // three modes.
-  QPass qa{}, qf{}, qx{};
-  bool has_qa = false, qf_two = false, has_qx = false;
-  // three modes: all p axes of a q point in one k_pcube task (then the q
-  // passes are (q_2, q_3) and q_1 alone, and excitations need no qx)
-  bool pcube = false, pcube_split = false, pcube_stream = false;
-  PCube pcb{};
-  // Hermite basis: k_hcube over the q cube of each (branch, element, k)
-  bool hcube = false, hcube_split = false;
-  PCube hcb{};
-  int hcube_threads = 0, hcube_nb1 = 0;
-  int pcube_threads = 0, pcube_nb1 = 0;
-  size_t pcube_lds = 0;
-  int qa_threads = 0, qf_threads = 0, qx_threads = 0;
-  size_t qa_lds = 0, qf_lds = 0;
-  int qa_nmax = 48, qf_nmax = 48, qx_nmax = 48;
-};
-
-int pad8(int n) { return (n + 7) / 8 * 8; }
-// k_hcube grid: a multiple of 8 chunks when the tasks go to the XCDs in chunks
-int hcube_nblk(int ntasks, int chunk) { return chunk > 0 ? (ntasks + 8 * chunk - 1) / (8 * chunk) * (8 * chunk) : pad8(ntasks); }
-
 // Tile shapes the autotuner picked, kept per problem shape for the rest of
 // the process (later contexts of the same shape start from them).
 struct TileChoice {
@@ -385,61 +328,7 @@ std::vector<long long> tune_key(const Derived &d) {
   return k;
 }
 
-
 }  // namespace
-
-struct chfpe_ctx {
-  chfpe_params prm;
-  Derived d;
-  Layout L;
-  Launch ln;
-  Geom g;
-  Tabs tb;
-  hipStream_t stream = nullptr;
-  unsigned char *ws = nullptr;
-  bool own_ws = false;
-  double *F, *VpQ, *Vp, *pm, *pg, *gA, *gB, *gC, *Cw, *wp, *sq, *sp, *cc, *tc, *damp, *partial, *scal;
-  int *up, *dn, *flag;
-  double *weq, *u, *y, *xa, *xb, *t;
-  void *bb[kBranchBufs] = {nullptr, nullptr, nullptr, nullptr};  // batched y, xa, xb, t
-  // cached graph of one wave's t2 loop
-  hipGraphExec_t wave_graph = nullptr;
-  long long wave_key[6] = {0, 0, 0, 0, 0, 0};
-  bool has_eq = false;
-  double dV = 1.0;
-  std::vector<double> qgrid[3], pgrid[3];
-  std::vector<double> wq_host;  // q-point weights (product over q axes), Q entries
-  std::vector<double> sq_host;  // exp(-beta U(q)/2), Q entries
-  double *rbuf = nullptr;
-  size_t rbuf_cap = 0;
-  std::string err = "no error";
-  int tune_pb_nb = 0;   // blocks per k_pblock task (0: automatic)
-  int tune_q_pc = 0;    // run positions per two-axis k_qpass tile (0: automatic)
-  int tune_pb_split = -1;  // k_pblock lines solved by lane pairs (-1: automatic)
-  int tune_pb_run = 0;     // k_pblock consecutive block groups per state in task order (0: 1)
-  int tune_pc_pad = 0;     // k_pcube LDS plane row pad (0: 1)
-  int tune_pc_stream = -1;  // k_pcube_s (1) or k_pcube (0); -1: by the p_1 length
-  int tune_hc_chunk = -1;   // k_hcube tasks per XCD chunk (0: one contiguous range per XCD; -1: automatic)
-  int tune_hc_ktile = 0;    // k_hcube k_2 tile of the task order (0: automatic)
-  bool capturing = false;  // a HIP graph is being captured: no event timing
-  bool closure_on = false; // right-hand sides use the closure stencil weights (tb.clos)
-  bool use_graphs = true;
-  bool allow_pcube = true;  // three modes: k_pcube where the p block fits it
-  // kernel timing
-  int timing_every = 0;
-  long long step_counter = 0;
-  bool timing_now = false;
-  struct Pending {
-    hipEvent_t a, b;
-    int kind;
-    double bytes;
-  };
-  std::vector<Pending> pending;
-  std::vector<hipEvent_t> event_pool;
-  long long kcount[kNumKinds] = {0};
-  double ktime[kNumKinds] = {0};
-  double kbytes[kNumKinds] = {0};
-};
 
 namespace {
 
@@ -668,19 +557,6 @@ void plan_one(chfpe_ctx *c, int a, int run, std::vector<int> rest, QPass &out, i
   nmax = nmax_bucket(axis_len(c->d, a));
 }
 
-// LDS of a k_pcube workgroup: a copy of the task's p block, and two fields
-// of one round's (p_2, p_3) planes with rows of N_3 + pad values.  The
-// streamed form (k_pcube_s) keeps no copy: its planes, and the first
-// forward results of every p_1 line.
-size_t pcube_lds_bytes(const Derived &d, size_t tsize, int pad, bool stream) {
-  const int nb1 = nmax_bucket(d.Np[0]);
-  const size_t rows = (size_t)d.Np[1] * (size_t)(pcube_n3(d) + pad);
-  if (stream)
-    return (kPCubeCF + 2 * (size_t)pcube_s_planes(nb1) * rows +
-            (size_t)pcube_s_dlds((int)tsize, nb1) * d.Np[1] * pcube_n3(d)) * tsize;
-  return ((size_t)d.P + 2 * (size_t)pcube_planes(nb1) * rows + (size_t)d.Np[0]) * tsize;  // + the p_1 table
-}
-
 // Three modes take k_pcube wherever its block fits (CHFPE_PCUBE=0 keeps the
 // p-block path where that one tiles); two modes take it only for p blocks
 // the p-block tile cannot cover (p axes above 32 points).
@@ -718,6 +594,23 @@ bool plan(chfpe_ctx *c) {
     ln.hcube_nb1 = nmax_bucket(h.N1);
     ln.hcube_threads = (h.plane + 63) / 64 * 64;
     ln.hcube_split = h.N1 == ln.hcube_nb1 && h.N2 == h.N1 && h.N3 == h.N1;
+    // the wave-plane form, where the launch over every state fits one dispatch;
+    // two modes take the q grid as one (q_1, q_2) plane
+    ln.hwave = false;
+    ln.hwave_nb = nmax_bucket(*std::max_element(d.Nq, d.Nq + M));
+    if (M >= 2 && ln.hwave_nb <= (M == 3 ? 24 : 32)) {
+      PCube hw = h;
+      if (M == 2) {
+        hw.N1 = 1;
+        hw.N2 = d.Nq[0];
+        hw.N3 = d.Nq[1];
+        hw.plane = hw.N2 * hw.N3;
+      }
+      const int nw = hwave_nw(d, hw, ln.hwave_nb);
+      const long long tasks = (long long)h.ntasks * (d.batched ? d.B : 1);
+      ln.hwave = grid_items((M == 2 ? (tasks + nw - 1) / nw : tasks) + 8 * kMaxHcChunk, 64 * nw) <= kMaxGridItems;
+      if (ln.hwave) h = hw;
+    }
     return true;
   }
   const int NpM = d.Np[M - 1];
@@ -779,8 +672,11 @@ bool plan(chfpe_ctx *c) {
     // row pad of the LDS planes (CHFPE_TUNE_PC_PAD, 1..8), kept only while the LDS fits
     // the streamed form where its workgroups gain occupancy (p_1 up to 16
     // points: four-wave workgroups); CHFPE_TUNE_PC_STREAM=0/1 forces either
-    ln.pcube_stream = c->tune_pc_stream >= 0 ? (c->tune_pc_stream > 0 && nmax_bucket(d.Np[0]) <= 32)
-                                             : nmax_bucket(d.Np[0]) <= 16;
+    ln.pwave_nb = nmax_bucket(std::max(pq.N1, std::max(pq.N2, pq.N3)));
+    ln.pwave = M == 3 && ln.pwave_nb <= 24 && c->tune_pc_stream != 0 &&
+               grid_items((long long)pq.ntasks * nbat, 64 * pwave_nw(pq, ln.pwave_nb)) <= kMaxGridItems;
+    ln.pcube_stream = ln.pwave || (c->tune_pc_stream >= 0 ? (c->tune_pc_stream > 0 && nmax_bucket(d.Np[0]) <= 32)
+                                                          : nmax_bucket(d.Np[0]) <= 16);
     pq.rs = pq.N3 + 1;
     if (!ln.pcube_stream && c->tune_pc_pad > 1 && pcube_lds_bytes(d, sizeof(double), c->tune_pc_pad, false) <= 160 * 1024)
       pq.rs = pq.N3 + c->tune_pc_pad;
@@ -883,21 +779,6 @@ struct TimedScope {
   }
 };
 
-template <typename K>
-void allow_lds(K kern, size_t bytes) {
-  if (bytes > 64 * 1024)
-    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-}
-
-// A launch description for nb states stored back to back (t1 branches).
-struct Batch {
-  Geom g;
-  PBlock pb;
-  PCube pcb, hcb;
-  QPass qa, qf, qx;
-};
-
 Batch batch_of(const chfpe_ctx *c, int nb) {
   Batch b;
   b.g = c->g;
@@ -921,178 +802,6 @@ Batch batch_of(const chfpe_ctx *c, int nb) {
   return b;
 }
 
-// Closure variants of the kernels exist for FP64 states with every axis in a
-// bucket of at most 16 points (chfpe_set_closure enforces this).
-template <typename T, typename TO, int NMAX>
-constexpr bool kClosureBuilt = std::is_same<T, double>::value && std::is_same<TO, double>::value && NMAX <= 16;
-
-template <typename T, typename TO, int NMAX, int RPT, int MM, bool PERTURB>
-void launch_pblock_rpt(chfpe_ctx *c, const Batch &b, const T *X, TO *out, const double *grad) {
-  const Launch &ln = c->ln;
-  if constexpr (kClosureBuilt<T, TO, NMAX>) {
-    if (c->closure_on) {
-      auto kern = k_pblock<T, TO, NMAX, RPT, MM, PERTURB, true>;
-      allow_lds(kern, ln.pb_lds);
-      hipLaunchKernelGGL(kern, dim3(b.pb.nblk), dim3(ln.pb_threads), ln.pb_lds, c->stream, b.g, c->tb, b.pb,
-                         X, out, grad);
-      return;
-    }
-  }
-  auto kern = k_pblock<T, TO, NMAX, RPT, MM, PERTURB>;
-  allow_lds(kern, ln.pb_lds);
-  hipLaunchKernelGGL(kern, dim3(b.pb.nblk), dim3(ln.pb_threads), ln.pb_lds, c->stream, b.g, c->tb, b.pb, X,
-                     out, grad);
-}
-
-template <typename T, typename TO, int NMAX, int MM, bool PERTURB>
-void launch_pblock_nm(chfpe_ctx *c, const Batch &b, const T *X, TO *out, const double *grad) {
-  if constexpr (NMAX == 24 && MM >= 2) {
-    if (c->ln.pb_rpt == 3) {
-      launch_pblock_rpt<T, TO, NMAX, 3, MM, PERTURB>(c, b, X, out, grad);
-      return;
-    }
-  }
-  launch_pblock_rpt<T, TO, NMAX, kPBlockRPT, MM, PERTURB>(c, b, X, out, grad);
-}
-
-template <typename T, typename TO, int NMAX, bool PERTURB>
-void launch_pblock_n(chfpe_ctx *c, const Batch &b, const T *X, TO *out, const double *grad) {
-  switch (c->d.M) {
-    case 1: launch_pblock_nm<T, TO, NMAX, 1, PERTURB>(c, b, X, out, grad); break;
-    case 2: launch_pblock_nm<T, TO, NMAX, 2, PERTURB>(c, b, X, out, grad); break;
-    default: launch_pblock_nm<T, TO, NMAX, 3, PERTURB>(c, b, X, out, grad); break;
-  }
-}
-
-template <typename T, typename TO, bool PERTURB>
-void launch_pblock_t(chfpe_ctx *c, const Batch &b, const T *X, TO *out, const double *grad) {
-  switch (c->ln.pb_nmax) {
-    case 8: launch_pblock_n<T, TO, 8, PERTURB>(c, b, X, out, grad); break;
-    case 12: launch_pblock_n<T, TO, 12, PERTURB>(c, b, X, out, grad); break;
-    case 16: launch_pblock_n<T, TO, 16, PERTURB>(c, b, X, out, grad); break;
-    case 24: launch_pblock_n<T, TO, 24, PERTURB>(c, b, X, out, grad); break;
-    case 32: launch_pblock_n<T, TO, 32, PERTURB>(c, b, X, out, grad); break;
-    default: launch_pblock_n<T, TO, 48, PERTURB>(c, b, X, out, grad); break;
-  }
-}
-
-template <typename K, typename T, typename TO>
-void launch_pcube_k(chfpe_ctx *c, K kern, size_t lds, const Batch &b, const T *X, TO *out, const double *grad) {
-  allow_lds(kern, lds);
-  hipLaunchKernelGGL(kern, dim3(b.pcb.nblk), dim3(c->ln.pcube_threads), lds, c->stream, b.g, c->tb, b.pcb,
-                     X, out, grad);
-}
-
-// k_pcube, or its streamed form k_pcube_s where the plan chose it (p_1 axes
-// up to 32 points, plain stencils; closure tables take k_pcube)
-template <typename T, typename TO, int NB1, bool SPLIT, bool PERTURB>
-void launch_pcube_s(chfpe_ctx *c, const Batch &b, const T *X, TO *out, const double *grad) {
-  const int pad = b.pcb.rs - b.pcb.N3;
-  if constexpr (kClosureBuilt<T, TO, NB1>) {
-    if (c->closure_on) {
-      launch_pcube_k(c, k_pcube<T, TO, NB1, SPLIT, PERTURB, true>, pcube_lds_bytes(c->d, sizeof(T), pad, false),
-                     b, X, out, grad);
-      return;
-    }
-  }
-  if constexpr (NB1 <= 32) {
-    if (c->ln.pcube_stream) {
-      launch_pcube_k(c, k_pcube_s<T, TO, NB1, SPLIT, PERTURB>, pcube_lds_bytes(c->d, sizeof(T), pad, true), b, X,
-                     out, grad);
-      return;
-    }
-  }
-  launch_pcube_k(c, k_pcube<T, TO, NB1, SPLIT, PERTURB>, pcube_lds_bytes(c->d, sizeof(T), pad, false), b, X, out,
-                 grad);
-}
-
-template <typename T, typename TO, int NB1, bool PERTURB>
-void launch_pcube_n(chfpe_ctx *c, const Batch &b, const T *X, TO *out, const double *grad) {
-  if (c->ln.pcube_split)
-    launch_pcube_s<T, TO, NB1, true, PERTURB>(c, b, X, out, grad);
-  else
-    launch_pcube_s<T, TO, NB1, false, PERTURB>(c, b, X, out, grad);
-}
-
-template <typename T, typename TO, bool PERTURB>
-void launch_pcube_t(chfpe_ctx *c, const Batch &b, const T *X, TO *out, const double *grad) {
-  switch (c->ln.pcube_nb1) {
-    case 8: launch_pcube_n<T, TO, 8, PERTURB>(c, b, X, out, grad); break;
-    case 12: launch_pcube_n<T, TO, 12, PERTURB>(c, b, X, out, grad); break;
-    case 16: launch_pcube_n<T, TO, 16, PERTURB>(c, b, X, out, grad); break;
-    case 24: launch_pcube_n<T, TO, 24, PERTURB>(c, b, X, out, grad); break;
-    case 32: launch_pcube_n<T, TO, 32, PERTURB>(c, b, X, out, grad); break;
-    default: launch_pcube_n<T, TO, 48, PERTURB>(c, b, X, out, grad); break;
-  }
-}
-
-template <typename T, typename TO, int NMAX, bool TWO, int EPI, int FA, int FB>
-void launch_q_n(chfpe_ctx *c, const Batch &b, const QPass &qp, int threads, size_t lds, const T *X, TO *Tacc,
-                const TO *y, TO *xo, const double *grad, double cst) {
-  if constexpr (kClosureBuilt<T, TO, NMAX>) {
-    if (c->closure_on) {
-      auto kern = k_qpass<T, TO, NMAX, TWO, EPI, FA, FB, true>;
-      allow_lds(kern, lds);
-      hipLaunchKernelGGL(kern, dim3(qp.nblk), dim3(threads), lds, c->stream, b.g, c->tb, qp, X, Tacc, y, xo,
-                         grad, cst);
-      return;
-    }
-  }
-  auto kern = k_qpass<T, TO, NMAX, TWO, EPI, FA, FB>;
-  allow_lds(kern, lds);
-  hipLaunchKernelGGL(kern, dim3(qp.nblk), dim3(threads), lds, c->stream, b.g, c->tb, qp, X, Tacc, y, xo, grad,
-                     cst);
-}
-
-template <typename T, typename TO, bool TWO, int EPI, int FA, int FB>
-void launch_q_t(chfpe_ctx *c, const Batch &b, const QPass &qp, int threads, size_t lds, int nmax, const T *X,
-                TO *Tacc, const TO *y, TO *xo, const double *grad, double cst) {
-#define CHFPE_QN(N) launch_q_n<T, TO, N, TWO, EPI, FA, FB>(c, b, qp, threads, lds, X, Tacc, y, xo, grad, cst)
-  switch (nmax) {
-    case 8: CHFPE_QN(8); break;
-    case 12: CHFPE_QN(12); break;
-    case 16: CHFPE_QN(16); break;
-    case 24: CHFPE_QN(24); break;
-    case 32: CHFPE_QN(32); break;
-    default: CHFPE_QN(48); break;
-  }
-#undef CHFPE_QN
-}
-
-// Hermite basis: one k_hcube launch computes the right-hand side of X and
-// the stage update (EPI, coefficient cst) over every (branch, element, k).
-template <typename T, int NB1, bool SPLIT, int EPI>
-void launch_hcube_k(chfpe_ctx *c, const Batch &b, const T *X, const T *y, T *xo, double cst) {
-  const size_t lds = (kHCubeCF + 2 * (size_t)kHCubePL * b.hcb.N2 * b.hcb.rs) * sizeof(T);
-  auto kern = k_hcube<T, NB1, SPLIT, EPI>;
-  allow_lds(kern, lds);
-  hipLaunchKernelGGL(kern, dim3(b.hcb.nblk), dim3(c->ln.hcube_threads), lds, c->stream, b.g, c->tb, b.hcb, X, y,
-                     xo, cst);
-}
-
-template <typename T, int NB1, int EPI>
-void launch_hcube_n(chfpe_ctx *c, const Batch &b, const T *X, const T *y, T *xo, double cst) {
-  if constexpr (NB1 <= 24) {  // cubes of 32 or 48 points exceed the workgroup: never lane pairs
-    if (c->ln.hcube_split) {
-      launch_hcube_k<T, NB1, true, EPI>(c, b, X, y, xo, cst);
-      return;
-    }
-  }
-  launch_hcube_k<T, NB1, false, EPI>(c, b, X, y, xo, cst);
-}
-
-template <typename T, int EPI>
-void launch_hcube(chfpe_ctx *c, const Batch &b, const T *X, const T *y, T *xo, double cst) {
-  switch (c->ln.hcube_nb1) {
-    case 8: launch_hcube_n<T, 8, EPI>(c, b, X, y, xo, cst); break;
-    case 12: launch_hcube_n<T, 12, EPI>(c, b, X, y, xo, cst); break;
-    case 16: launch_hcube_n<T, 16, EPI>(c, b, X, y, xo, cst); break;
-    case 24: launch_hcube_n<T, 24, EPI>(c, b, X, y, xo, cst); break;
-    case 32: launch_hcube_n<T, 32, EPI>(c, b, X, y, xo, cst); break;
-    default: launch_hcube_n<T, 48, EPI>(c, b, X, y, xo, cst); break;
-  }
-}
-
 // One right-hand-side evaluation of X (t: partial right-hand side) fused with
 // the stage epilogue EPI (coefficient cst); all buffers hold b.g.nbatch
 // states.  kind: the timing kind of the stage-final launch.
@@ -1103,12 +812,18 @@ void launch_stage(chfpe_ctx *c, const Batch &b, const T *X, T *t, const T *y, T 
     const int hk = EPI == EPI_H1 ? K_HS1 : EPI == EPI_H4 ? K_HS4 : EPI == EPI_OUT ? K_HOUT
                    : kind == K_QS3 ? K_HS3 : K_HS2;
     TimedScope ts(c, hk, b.g.nbatch, sizeof(T));
-    launch_hcube<T, EPI>(c, b, X, y, xo, cst);
+    if (ln.hwave)
+      launch_hwave<T>(c, b, X, y, xo, cst, EPI);
+    else
+      launch_hcube<T, EPI>(c, b, X, y, xo, cst);
     return;
   }
   if (ln.pcube) {
     TimedScope ts(c, K_PCUBE, b.g.nbatch, sizeof(T));
-    launch_pcube_t<T, T, false>(c, b, X, t, nullptr);
+    if (ln.pwave)
+      launch_pwave<T, T, false>(c, b, X, t, nullptr);
+    else
+      launch_pcube_t<T, T, false>(c, b, X, t, nullptr);
   } else {
     TimedScope ts(c, K_PBLOCK, b.g.nbatch, sizeof(T));
     launch_pblock_t<T, T, false>(c, b, X, t, nullptr);
@@ -1140,7 +855,10 @@ void launch_perturb(chfpe_ctx *c, const double *W, TO *out, const double *grad) 
     return;
   }
   if (c->ln.pcube) {
-    launch_pcube_t<double, TO, true>(c, b, W, out, grad);
+    if (c->ln.pwave)
+      launch_pwave<double, TO, true>(c, b, W, out, grad);
+    else
+      launch_pcube_t<double, TO, true>(c, b, W, out, grad);
     return;
   }
   launch_pblock_t<double, TO, true>(c, b, W, out, grad);

@@ -1,0 +1,191 @@
+// State of a solver context and the launch plan, shared by the host side
+// (chfpe.hip) and the launchers of the kernel families (launch_*.hip).
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cstdlib>
+#include <string>
+#include <type_traits>
+#include <vector>
+
+#include "chfpe.h"
+#include "kernels.h"
+#include "wave.h"
+
+namespace chfpe {
+
+constexpr int kPBlockRPT = 4;        // rows per k_pblock thread
+constexpr int kNumBase = 15;         // kernel kinds of the event timing (see Kind in chfpe.hip)
+constexpr int kNumKinds = 2 * kNumBase;
+
+struct Derived {
+  int prec = 0, B = 1;    // precision of branch states; branches per wave
+  bool batched = false;   // 2D responses use the batched branch buffers
+  bool hermite = false;   // Hermite basis in p: P counts Hermite functions, layout [n][k][q]
+  int M = 0, K = 0, ne = 0;
+  int Nq[3] = {0, 0, 0}, Np[3] = {0, 0, 0};  // axes s >= M stay 0
+  int Q = 0, P = 0;
+  long long E, S;  // points per element, values per state
+  std::vector<int> nvec;  // ne * M
+};
+
+inline int nmax_bucket(int n) {
+  return n <= 8 ? 8 : n <= 12 ? 12 : n <= 16 ? 16 : n <= 24 ? 24 : n <= 32 ? 32 : 48;
+}
+
+inline int pcube_n3(const Derived &d) { return d.M == 3 ? d.Np[2] : 1; }
+
+constexpr int kStateBufs = 6;   // FP64: W_eq, U, y, xa, xb, t
+constexpr int kBranchBufs = 4;  // per branch of a wave: y, xa, xb, t
+
+// Workspace layout (byte offsets, 256-aligned).
+struct Layout {
+  size_t F, VpQ, Vp, pm, pg, gA, gB, gC, Cw, wp, sq, sp, up, dn, cc, tc, damp, partial, scal, flag, clos;
+  size_t bufs[kStateBufs];
+  size_t bbufs[kBranchBufs];  // batched branch buffers: y, xa, xb, t (B states each)
+  size_t total;
+};
+struct Launch {
+  PBlock pb{};
+  size_t pb_lds = 0;
+  int pb_threads = 256, pb_nmax = 48;
+  int pb_rpt = 4;  // rows per k_pblock thread (3 where it tiles the 24-row blocks exactly)
+  // strided-axis passes of one stage: qa (three modes only, accumulates into
+  // t) then qf (applies the stage update); qx: the p_1 excitation pass of
+  // three modes.
+  QPass qa{}, qf{}, qx{};
+  bool has_qa = false, qf_two = false, has_qx = false;
+  // three modes: all p axes of a q point in one k_pcube task (then the q
+  // passes are (q_2, q_3) and q_1 alone, and excitations need no qx)
+  bool pcube = false, pcube_split = false, pcube_stream = false;
+  bool pwave = false;  // the streamed form is k_pwave (p axes of at most 24 points)
+  int pwave_nb = 0;
+  PCube pcb{};
+  // Hermite basis: k_hcube over the q cube of each (branch, element, k)
+  bool hcube = false, hcube_split = false;
+  PCube hcb{};
+  int hcube_threads = 0, hcube_nb1 = 0;
+  bool hwave = false;  // k_hwave (three modes, q axes of at most 24 points; two modes, 32)
+  int hwave_nb = 0;
+  int pcube_threads = 0, pcube_nb1 = 0;
+  size_t pcube_lds = 0;
+  int qa_threads = 0, qf_threads = 0, qx_threads = 0;
+  size_t qa_lds = 0, qf_lds = 0;
+  int qa_nmax = 48, qf_nmax = 48, qx_nmax = 48;
+};
+
+inline int pad8(int n) { return (n + 7) / 8 * 8; }
+// k_hcube grid: a multiple of 8 chunks when the tasks go to the XCDs in chunks
+inline int hcube_nblk(int ntasks, int chunk) { return chunk > 0 ? (ntasks + 8 * chunk - 1) / (8 * chunk) * (8 * chunk) : pad8(ntasks); }
+
+}  // namespace chfpe
+
+using namespace chfpe;
+
+struct chfpe_ctx {
+  chfpe_params prm;
+  Derived d;
+  Layout L;
+  Launch ln;
+  Geom g;
+  Tabs tb;
+  hipStream_t stream = nullptr;
+  unsigned char *ws = nullptr;
+  bool own_ws = false;
+  double *F, *VpQ, *Vp, *pm, *pg, *gA, *gB, *gC, *Cw, *wp, *sq, *sp, *cc, *tc, *damp, *partial, *scal;
+  int *up, *dn, *flag;
+  double *weq, *u, *y, *xa, *xb, *t;
+  void *bb[kBranchBufs] = {nullptr, nullptr, nullptr, nullptr};  // batched y, xa, xb, t
+  // cached graph of one wave's t2 loop
+  hipGraphExec_t wave_graph = nullptr;
+  long long wave_key[6] = {0, 0, 0, 0, 0, 0};
+  bool has_eq = false;
+  double dV = 1.0;
+  std::vector<double> qgrid[3], pgrid[3];
+  std::vector<double> wq_host;  // q-point weights (product over q axes), Q entries
+  std::vector<double> sq_host;  // exp(-beta U(q)/2), Q entries
+  double *rbuf = nullptr;
+  size_t rbuf_cap = 0;
+  std::string err = "no error";
+  int tune_pb_nb = 0;   // blocks per k_pblock task (0: automatic)
+  int tune_q_pc = 0;    // run positions per two-axis k_qpass tile (0: automatic)
+  int tune_pb_split = -1;  // k_pblock lines solved by lane pairs (-1: automatic)
+  int tune_pb_run = 0;     // k_pblock consecutive block groups per state in task order (0: 1)
+  int tune_pc_pad = 0;     // k_pcube LDS plane row pad (0: 1)
+  int tune_pc_stream = -1;  // k_pcube_s (1) or k_pcube (0); -1: by the p_1 length
+  int tune_hc_chunk = -1;   // k_hcube tasks per XCD chunk (0: one contiguous range per XCD; -1: automatic)
+  int tune_hc_ktile = 0;    // k_hcube k_2 tile of the task order (0: automatic)
+  bool capturing = false;  // a HIP graph is being captured: no event timing
+  bool closure_on = false; // right-hand sides use the closure stencil weights (tb.clos)
+  bool use_graphs = true;
+  bool allow_pcube = true;  // three modes: k_pcube where the p block fits it
+  // kernel timing
+  int timing_every = 0;
+  long long step_counter = 0;
+  bool timing_now = false;
+  struct Pending {
+    hipEvent_t a, b;
+    int kind;
+    double bytes;
+  };
+  std::vector<Pending> pending;
+  std::vector<hipEvent_t> event_pool;
+  long long kcount[kNumKinds] = {0};
+  double ktime[kNumKinds] = {0};
+  double kbytes[kNumKinds] = {0};
+};
+
+namespace chfpe {
+
+// LDS of a k_pcube workgroup: a copy of the task's p block, and two fields
+// of one round's (p_2, p_3) planes with rows of N_3 + pad values.  The
+// streamed form (k_pcube_s) keeps no copy: its planes, and the first
+// forward results of every p_1 line.
+inline size_t pcube_lds_bytes(const Derived &d, size_t tsize, int pad, bool stream) {
+  const int nb1 = nmax_bucket(d.Np[0]);
+  const size_t rows = (size_t)d.Np[1] * (size_t)(pcube_n3(d) + pad);
+  if (stream)
+    return (kPCubeCF + 2 * (size_t)pcube_s_planes(nb1) * rows +
+            (size_t)pcube_s_dlds((int)tsize, nb1) * d.Np[1] * pcube_n3(d)) * tsize;
+  return ((size_t)d.P + 2 * (size_t)pcube_planes(nb1) * rows + (size_t)d.Np[0]) * tsize;  // + the p_1 table
+}
+
+// Waves of a k_pwave workgroup.
+inline int pwave_nw(const PCube &p, int nb) {
+  const bool exact = p.N1 == nb && p.N2 == nb && p.N3 == nb;
+  const int per = wave_ps(nb, exact) * pwave_npw(nb, exact);
+  return (p.N1 + per - 1) / per;
+}
+
+// Waves of a k_hwave workgroup, and its workgroups for ntasks tasks (two
+// modes: a wave per task).
+inline int hwave_nw(const Derived &d, const PCube &p, int nb) {
+  const bool exact = (d.M == 2 || p.N1 == nb) && p.N2 == nb && p.N3 == nb;
+  if (d.M == 2) return hwave_waves(nb, exact, 2);
+  const int per = hwave_ps(nb, exact, 3) * hwave_npw(nb, exact, 3);
+  return (p.N1 + per - 1) / per;
+}
+
+template <typename K>
+void allow_lds(K kern, size_t bytes) {
+  if (bytes > 64 * 1024)
+    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+}
+
+// A launch description for nb states stored back to back (t1 branches).
+struct Batch {
+  Geom g;
+  PBlock pb;
+  PCube pcb, hcb;
+  QPass qa, qf, qx;
+};
+
+// Closure variants of the kernels exist for FP64 states with every axis in a
+// bucket of at most 16 points (chfpe_set_closure enforces this).
+template <typename T, typename TO, int NMAX>
+constexpr bool kClosureBuilt = std::is_same<T, double>::value && std::is_same<TO, double>::value && NMAX <= 16;
+
+}  // namespace chfpe

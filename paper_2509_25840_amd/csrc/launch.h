@@ -1,0 +1,26 @@
+// Launchers of the kernel families, one translation unit each.
+#pragma once
+
+#include "context.h"
+
+namespace chfpe {
+
+// p side of a right-hand side (PERTURB: of X^x, dX/dq_s in grad): out from X.
+template <typename T, typename TO, bool PERTURB>
+void launch_pblock_t(chfpe_ctx *c, const Batch &b, const T *X, TO *out, const double *grad);
+template <typename T, typename TO, bool PERTURB>
+void launch_pcube_t(chfpe_ctx *c, const Batch &b, const T *X, TO *out, const double *grad);
+template <typename T, typename TO, bool PERTURB>
+void launch_pwave(chfpe_ctx *c, const Batch &b, const T *X, TO *out, const double *grad);
+// k_qpass over the axes of qp.
+template <typename T, typename TO, bool TWO, int EPI, int FA, int FB>
+void launch_q_t(chfpe_ctx *c, const Batch &b, const QPass &qp, int threads, size_t lds, int nmax, const T *X,
+                TO *Tacc, const TO *y, TO *xo, const double *grad, double cst);
+// Hermite basis: the right-hand side of X and the stage update (EPI,
+// coefficient cst) over every (branch, element, k).
+template <typename T, int EPI>
+void launch_hcube(chfpe_ctx *c, const Batch &b, const T *X, const T *y, T *xo, double cst);
+template <typename T>
+void launch_hwave(chfpe_ctx *c, const Batch &b, const T *X, const T *y, T *xo, double cst, int epi);
+
+}  // namespace chfpe

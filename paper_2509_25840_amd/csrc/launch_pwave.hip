@@ -1,0 +1,59 @@
+// Launches of k_pwave.
+#include "launch.h"
+
+namespace chfpe {
+
+// k_pwave (three modes): a cube whose axes all have NB points (NVR = 0), or any
+// block of axes of at most NB points with planes of at most 64 NVR points.
+template <typename T, typename TO, int NB, int NVR, bool PERTURB>
+void launch_pwave_k(chfpe_ctx *c, const Batch &b, const T *X, TO *out, const double *grad) {
+  const int nw = pwave_nw(b.pcb, NB);
+  const size_t lds = sizeof(T) * pwave_lds_vals(NB, b.pcb.N1, b.pcb.N2, b.pcb.N3, nw, wave_ps(NB, NVR == 0),
+                                                c->closure_on);
+  if constexpr (kClosureBuilt<T, TO, NB>) {
+    if (c->closure_on) {
+      auto kern = k_pwave<T, TO, NB, NVR, PERTURB, true>;
+      allow_lds(kern, lds);
+      hipLaunchKernelGGL(kern, dim3(b.pcb.nblk), dim3(64 * nw), lds, c->stream, b.g, c->tb, b.pcb, X, out, grad);
+      return;
+    }
+  }
+  auto kern = k_pwave<T, TO, NB, NVR, PERTURB>;
+  allow_lds(kern, lds);
+  hipLaunchKernelGGL(kern, dim3(b.pcb.nblk), dim3(64 * nw), lds, c->stream, b.g, c->tb, b.pcb, X, out, grad);
+}
+
+template <typename T, typename TO, int NB, bool PERTURB>
+void launch_pwave_n(chfpe_ctx *c, const Batch &b, const T *X, TO *out, const double *grad) {
+  constexpr int full = wave_nv(NB, 1, 1);  // vectors per lane of an NB x NB plane, one value each
+  if (b.pcb.N1 == NB && b.pcb.N2 == NB && b.pcb.N3 == NB) {
+    launch_pwave_k<T, TO, NB, 0, PERTURB>(c, b, X, out, grad);
+    return;
+  }
+  if constexpr (NB >= 24) {
+    if (b.pcb.plane <= 64 * 4) return launch_pwave_k<T, TO, NB, 4, PERTURB>(c, b, X, out, grad);
+    if (b.pcb.plane <= 64 * 6) return launch_pwave_k<T, TO, NB, 6, PERTURB>(c, b, X, out, grad);
+  }
+  if constexpr (NB == 16) {
+    if (b.pcb.plane <= 64 * 2) return launch_pwave_k<T, TO, NB, 2, PERTURB>(c, b, X, out, grad);
+  }
+  launch_pwave_k<T, TO, NB, full, PERTURB>(c, b, X, out, grad);
+}
+
+template <typename T, typename TO, bool PERTURB>
+void launch_pwave(chfpe_ctx *c, const Batch &b, const T *X, TO *out, const double *grad) {
+  switch (c->ln.pwave_nb) {
+    case 8: launch_pwave_n<T, TO, 8, PERTURB>(c, b, X, out, grad); break;
+    case 12: launch_pwave_n<T, TO, 12, PERTURB>(c, b, X, out, grad); break;
+    case 16: launch_pwave_n<T, TO, 16, PERTURB>(c, b, X, out, grad); break;
+    default: launch_pwave_n<T, TO, 24, PERTURB>(c, b, X, out, grad); break;
+  }
+}
+
+#define CHFPE_INST(T, TO, P) template void launch_pwave<T, TO, P>(chfpe_ctx *, const Batch &, const T *, TO *, const double *);
+CHFPE_INST(double, double, false)
+CHFPE_INST(float, float, false)
+CHFPE_INST(double, double, true)
+CHFPE_INST(double, float, true)
+
+}  // namespace chfpe
