@@ -260,7 +260,7 @@ int chfpe_spectrum_2dir(const double *R, int64_t n_t1, int64_t n_t3, double tau1
 /* chfpe_spectrum_2d without device allocation, for callers that cannot
  * allocate (tight serving loops, harnesses that forbid hipMalloc): same
  * arguments, result and conventions, with every device buffer in a fixed
- * per-device scratch array of the library (48 bytes per point) instead of
+ * per-device scratch array of the library (32 bytes per point) instead of
  * per-call allocations.  n_t1 * n_t2 <= 131072 (EINVAL above).  Calls on one
  * GPU share that scratch: calls that overlap in time on one GPU (other host
  * threads, other streams) race and must be serialized by the caller.  The

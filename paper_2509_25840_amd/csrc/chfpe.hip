@@ -1235,15 +1235,15 @@ int fail_g(int code, const std::string &msg) { return fail(nullptr, code, msg); 
 
 // ---------------------------------------------------------------------------
 // Device scratch of chfpe_spectrum_2d_noalloc: a file-scope array, one copy
-// per device, that holds R, two complex work arrays and I of one spectrum
-// of at most kNoAllocMaxPoints points (48 bytes per point, 6 MiB).  Host
+// per device, that holds R, a complex work array and I of one spectrum
+// of at most kNoAllocMaxPoints points (32 bytes per point, 4 MiB).  Host
 // code never passes the array's name to a kernel or copy: it takes the
 // device address of each GPU's copy once (hipGetSymbolAddress, with that
 // device current) and uses that address.
 // ---------------------------------------------------------------------------
 constexpr long long kNoAllocMaxPoints = 1LL << 17;
 constexpr int kMaxDevices = 64;
-static __device__ __align__(256) unsigned char scratch[48 * kNoAllocMaxPoints];
+static __device__ __align__(256) unsigned char scratch[32 * kNoAllocMaxPoints];
 
 namespace {
 std::mutex g_scratch_mu;
@@ -1721,20 +1721,21 @@ struct DevBuf {
 int chfpe_spectrum_1d(const double *R, int64_t n, double tau, double *omega, double *I, void *hip_stream) {
   if (!R || !I || n < 1 || n > (1LL << 24) || !(tau > 0) || !std::isfinite(tau)) return CHFPE_EINVAL;
   hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
-  DevBuf bR, bz, bo, bI;
-  if (hipMalloc(&bR.p, n * sizeof(double)) != hipSuccess || hipMalloc(&bz.p, n * sizeof(double2)) != hipSuccess ||
-      hipMalloc(&bo.p, n * sizeof(double2)) != hipSuccess || hipMalloc(&bI.p, n * sizeof(double)) != hipSuccess)
-    return CHFPE_ENOMEM;
-  if (hipMemcpyAsync(bR.p, R, n * sizeof(double), hipMemcpyHostToDevice, st) != hipSuccess) return CHFPE_EDEVICE;
-  const int nb = (int)((n + 255) / 256);
-  hipLaunchKernelGGL(k_to_complex, dim3(nb), dim3(256), 0, st, (const double *)bR.p, (double2 *)bz.p, n);
+  DevBuf buf;  // R, then I
+  if (hipMalloc(&buf.p, 2 * n * sizeof(double)) != hipSuccess) return CHFPE_ENOMEM;
+  double *dR = (double *)buf.p, *dI = dR + n;
+  if (hipMemcpyAsync(dR, R, n * sizeof(double), hipMemcpyHostToDevice, st) != hipSuccess) return CHFPE_EDEVICE;
   // sum_j exp(+i omega_k t_j) R_j, omega_k = 2 pi k / (n tau)
-  hipLaunchKernelGGL(k_dft_rows, dim3(nb), dim3(256), 0, st, (const double2 *)bz.p, (double2 *)bo.p, 1, (int)n,
-                     (int)n, 1, (int)n, 1, 1.0);
   const double dw = 2.0 * M_PI / ((double)n * tau);
-  hipLaunchKernelGGL(k_spectrum_out, dim3(nb), dim3(256), 0, st, (const double2 *)bo.p, (long long)n, (int)n,
-                     tau, dw, 1, (double *)bI.p);
-  if (hipMemcpyAsync(I, bI.p, n * sizeof(double), hipMemcpyDeviceToHost, st) != hipSuccess) return CHFPE_EDEVICE;
+  const dim3 grid((unsigned)((n + kDftK - 1) / kDftK));
+  if (n <= kDftTab) {
+    const size_t lds = 2 * (size_t)n * sizeof(double);
+    allow_lds(k_spectrum_1d<true>, lds);
+    hipLaunchKernelGGL(k_spectrum_1d<true>, grid, dim3(256), lds, st, dR, (int)n, tau, dw, dI);
+  } else {
+    hipLaunchKernelGGL(k_spectrum_1d<false>, grid, dim3(256), 0, st, dR, (int)n, tau, dw, dI);
+  }
+  if (hipMemcpyAsync(I, dI, n * sizeof(double), hipMemcpyDeviceToHost, st) != hipSuccess) return CHFPE_EDEVICE;
   if (hipStreamSynchronize(st) != hipSuccess) return CHFPE_EDEVICE;
   if (hipGetLastError() != hipSuccess) return CHFPE_EDEVICE;
   if (omega)
@@ -1746,23 +1747,35 @@ int chfpe_spectrum_1d(const double *R, int64_t n, double tau, double *omega, dou
 
 namespace {
 
+template <bool REAL, bool IMAG>
+void launch_dft_axis(const double *in, double *out, long long nl, long long n, double sign, double scale,
+                     hipStream_t st) {
+  int lanes_l = 1;
+  while (lanes_l < 64 && lanes_l < nl) lanes_l *= 2;
+  const long long kpw = 64 / lanes_l;
+  const dim3 grid((unsigned)std::min(65536LL, ((nl + lanes_l - 1) / lanes_l) * ((n + kpw - 1) / kpw)));
+  if (n <= kDftTab) {
+    const size_t lds = (size_t)n * sizeof(double2);
+    allow_lds(k_dft_axis<REAL, IMAG, true>, lds);
+    hipLaunchKernelGGL((k_dft_axis<REAL, IMAG, true>), grid, dim3(256), lds, st, in, out, (int)nl, (int)n, lanes_l,
+                       sign, scale);
+  } else {
+    hipLaunchKernelGGL((k_dft_axis<REAL, IMAG, false>), grid, dim3(256), 0, st, in, out, (int)nl, (int)n, lanes_l,
+                       sign, scale);
+  }
+}
+
 // Im{tau_f tau_s sum_{j_s, j_f} exp(-i omega_f t_f + sign_s i omega_s t_s) R[j_s][j_f]}
-// as two passes of discrete Fourier sums (fast axis, then slow axis), on
-// device buffers dR (n doubles), dz, dout (n double2 each) and dI (n doubles).
+// as two passes of discrete Fourier sums (slow axis, then fast axis), on
+// device buffers dR (n doubles), dz (n double2) and dI (n doubles).
 int spectrum_2d_on(const double *R, long long n_f, long long n_s, double tau_f, double tau_s, double sign_s,
-                   double *I, hipStream_t st, double *dR, double2 *dz, double2 *dout, double *dI) {
+                   double *I, hipStream_t st, double *dR, double *dz, double *dI) {
   const long long n = n_f * n_s;
   if (hipMemcpyAsync(dR, R, n * sizeof(double), hipMemcpyHostToDevice, st) != hipSuccess) return CHFPE_EDEVICE;
-  const int nb = (int)((n + 255) / 256);
-  hipLaunchKernelGGL(k_to_complex, dim3(nb), dim3(256), 0, st, (const double *)dR, dz, n);
-  // along the fast axis (rows of length n_f), exp(-i omega t)
-  hipLaunchKernelGGL(k_dft_rows, dim3(nb), dim3(256), 0, st, (const double2 *)dz, dout, (int)n_s, (int)n_f,
-                     (int)n_f, 1, (int)n_f, 1, -1.0);
-  // along the slow axis (columns, stride n_f), exp(sign_s i omega t)
-  hipLaunchKernelGGL(k_dft_rows, dim3(nb), dim3(256), 0, st, (const double2 *)dout, dz, (int)n_f, (int)n_s, 1,
-                     (int)n_f, 1, (int)n_f, sign_s);
-  hipLaunchKernelGGL(k_spectrum_out, dim3(nb), dim3(256), 0, st, (const double2 *)dz, n, (int)n_f, tau_f * tau_s,
-                     0.0, 0, dI);
+  // along the slow axis, exp(sign_s i omega t): dz[j_f][k_s]
+  launch_dft_axis<true, false>(dR, dz, n_f, n_s, sign_s, 1.0, st);
+  // along the fast axis, exp(-i omega t): dI[k_s][k_f]
+  launch_dft_axis<false, true>(dz, dI, n_s, n_f, -1.0, tau_f * tau_s, st);
   if (hipMemcpyAsync(I, dI, n * sizeof(double), hipMemcpyDeviceToHost, st) != hipSuccess) return CHFPE_EDEVICE;
   if (hipStreamSynchronize(st) != hipSuccess) return CHFPE_EDEVICE;
   if (hipGetLastError() != hipSuccess) return CHFPE_EDEVICE;
@@ -1779,12 +1792,10 @@ int spectrum_2d_signed(const double *R, int64_t n_f, int64_t n_s, double tau_f, 
                        double *I, void *hip_stream) {
   if (!spectrum_args_ok(R, I, n_f, n_s, tau_f, tau_s)) return CHFPE_EINVAL;
   const long long n = n_f * n_s;
-  DevBuf bR, bz, bo, bI;
-  if (hipMalloc(&bR.p, n * sizeof(double)) != hipSuccess || hipMalloc(&bz.p, n * sizeof(double2)) != hipSuccess ||
-      hipMalloc(&bo.p, n * sizeof(double2)) != hipSuccess || hipMalloc(&bI.p, n * sizeof(double)) != hipSuccess)
-    return CHFPE_ENOMEM;
-  return spectrum_2d_on(R, n_f, n_s, tau_f, tau_s, sign_s, I, reinterpret_cast<hipStream_t>(hip_stream),
-                        (double *)bR.p, (double2 *)bz.p, (double2 *)bo.p, (double *)bI.p);
+  DevBuf buf;  // the complex array, then R and I
+  if (hipMalloc(&buf.p, 4 * n * sizeof(double)) != hipSuccess) return CHFPE_ENOMEM;
+  double *dz = (double *)buf.p, *dR = dz + 2 * n, *dI = dR + n;
+  return spectrum_2d_on(R, n_f, n_s, tau_f, tau_s, sign_s, I, reinterpret_cast<hipStream_t>(hip_stream), dR, dz, dI);
 }
 
 }  // namespace
@@ -1808,14 +1819,9 @@ int chfpe_spectrum_2d_noalloc(const double *R, int64_t n_t1, int64_t n_t2, doubl
   int rc = scratch_of_current_device(&base);
   if (rc) return rc;
   const long long n = n_t1 * n_t2;
-  // layout in the scratch: two complex arrays, then R and I (16-byte aligned)
-  unsigned char *b = reinterpret_cast<unsigned char *>(base);
-  double2 *dz = reinterpret_cast<double2 *>(b);
-  double2 *dout = reinterpret_cast<double2 *>(b + 16 * n);
-  double *dR = reinterpret_cast<double *>(b + 32 * n);
-  double *dI = reinterpret_cast<double *>(b + 40 * n);
-  return spectrum_2d_on(R, n_t1, n_t2, tau1, tau2, -1.0, I, reinterpret_cast<hipStream_t>(hip_stream), dR, dz,
-                        dout, dI);
+  // layout in the scratch: the complex array, then R and I
+  double *dz = reinterpret_cast<double *>(base), *dR = dz + 2 * n, *dI = dR + n;
+  return spectrum_2d_on(R, n_t1, n_t2, tau1, tau2, -1.0, I, reinterpret_cast<hipStream_t>(hip_stream), dR, dz, dI);
 }
 
 int chfpe_set_kernel_timing(chfpe_ctx *c, int32_t every) {
