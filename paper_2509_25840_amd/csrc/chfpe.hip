@@ -649,6 +649,7 @@ bool plan(chfpe_ctx *c) {
   ln.pb_lds = (size_t)pb.NB * pb.tileP * sizeof(double);
   ln.pb_threads = pb.RG * pb.cols;
   // strided-axis passes
+  ln.one = one_shape_ok(d) && c->allow_one;
   if (M == 1) {
     ln.has_qa = false;
     ln.qf_two = false;
@@ -873,6 +874,10 @@ int last_launch_error(chfpe_ctx *c) {
   return CHFPE_OK;
 }
 
+// One mode: k_one instead of the launches of single stages (which kernel
+// timing and a closure keep).
+bool use_one(const chfpe_ctx *c) { return c->ln.one && c->timing_every == 0 && !c->closure_on; }
+
 // The buffers of one RK4 integration: y (in place), the alternating stage
 // states xa/xb, and the partial right-hand side t.
 template <typename T>
@@ -884,6 +889,10 @@ struct RK4Bufs {
 // polynomial of dt L in nested form (see Epi in kernels.h).
 template <typename T>
 int rk4(chfpe_ctx *c, const Batch &b, const RK4Bufs<T> &r, long long nsteps, double dt) {
+  if (use_one(c)) {
+    if (nsteps > 0) launch_one<T>(c, b.g.nbatch, r.y, 1, nsteps, false, dt, nullptr, 0, 0);
+    return last_launch_error(c);
+  }
   for (long long st = 0; st < nsteps; ++st) {
     c->timing_now = c->timing_every > 0 && (c->step_counter % c->timing_every) == 0;
     ++c->step_counter;
@@ -930,20 +939,38 @@ int observe_to(chfpe_ctx *c, const double *W, double *dst) {
   return CHFPE_OK;
 }
 
+// n samples of <C> of the states of b, `stride` RK4 steps before each but the
+// first: state k's sample j goes to dst[j * ostride + k].
+template <typename T>
+int sample(chfpe_ctx *c, const Batch &b, const RK4Bufs<T> &r, long long n, int stride, double dt, double *dst,
+           long long ostride) {
+  if (use_one(c)) {
+    launch_one<T>(c, b.g.nbatch, r.y, n, stride, true, dt, dst, ostride, 1);
+    return last_launch_error(c);
+  }
+  for (long long j = 0; j < n; ++j) {
+    if (j > 0) {
+      int rc = rk4<T>(c, b, r, stride, dt);
+      if (rc) return rc;
+    }
+    observe_batch<T>(c, r.y, b.g.nbatch, dst + j * ostride, 1);
+  }
+  return CHFPE_OK;
+}
+
+// The same for the FP64 single-state buffers (the state in c->y).
+int sample(chfpe_ctx *c, long long n, int stride, double dt, double *dst, long long ostride) {
+  const Batch b = batch_of(c, 1);
+  return sample<double>(c, b, RK4Bufs<double>{c->y, c->xa, c->xb, c->t}, n, stride, dt, dst, ostride);
+}
+
 // The t2 loop of one wave: nb branch states in the batched buffers, each
 // observed after every s2 steps; Rw[j2 * B + b] receives <C> of branch b.
 template <typename T>
 int enqueue_wave(chfpe_ctx *c, int nb, long long n_t2, int s2, double dt, double *Rw) {
   const Batch b = batch_of(c, nb);
   const RK4Bufs<T> r{(T *)c->bb[0], (T *)c->bb[1], (T *)c->bb[2], (T *)c->bb[3]};
-  for (long long j2 = 0; j2 < n_t2; ++j2) {
-    if (j2 > 0) {
-      int rc = rk4<T>(c, b, r, s2, dt);
-      if (rc) return rc;
-    }
-    observe_batch<T>(c, r.y, nb, Rw + j2 * c->d.B, 1);
-  }
-  return CHFPE_OK;
+  return sample<T>(c, b, r, n_t2, s2, dt, Rw, c->d.B);
 }
 
 // Run one wave, as a captured HIP graph when possible.  The executable graph
@@ -1352,6 +1379,7 @@ int chfpe_setup(const chfpe_params *p, void *dev_workspace, size_t ws_bytes, voi
   if (const char *v = std::getenv("CHFPE_TUNE_HC_KTILE")) c->tune_hc_ktile = std::atoi(v);
   if (const char *v = std::getenv("CHFPE_NO_GRAPH")) c->use_graphs = std::atoi(v) == 0;
   if (const char *v = std::getenv("CHFPE_PCUBE")) c->allow_pcube = std::atoi(v) != 0;
+  if (const char *v = std::getenv("CHFPE_ONE")) c->allow_one = std::atoi(v) != 0;
   std::vector<double> F, Vp, pm, pg, sq, sp, wp, cc, tc, damp;
   std::vector<int> up, dn;
   build_tables(c, F, Vp, pm, pg, sq, sp, wp, up, dn, cc, tc, damp);
@@ -1511,13 +1539,8 @@ int chfpe_response_1d(chfpe_ctx *c, const chfpe_optical *A, int64_t n_t, int32_t
   HIPCHK(c, hipMemcpyAsync(c->gA, gt.data(), gt.size() * sizeof(double), hipMemcpyHostToDevice, c->stream));
   HIPCHK(c, hipMemcpyAsync(c->Cw, ct.data(), ct.size() * sizeof(double), hipMemcpyHostToDevice, c->stream));
   launch_perturb<double>(c, c->weq, c->y, c->gA);
-  for (int64_t j = 0; j < n_t; ++j) {
-    if (j > 0) {
-      rc = rk4(c, c->y, stride, dt);
-      if (rc) return rc;
-    }
-    observe_to(c, c->y, c->rbuf + j);
-  }
+  rc = sample(c, n_t, stride, dt, c->rbuf, 1);
+  if (rc) return rc;
   HIPCHK(c, hipMemcpyAsync(R, c->rbuf, n_t * sizeof(double), hipMemcpyDeviceToHost, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
   rc = last_launch_error(c);
@@ -1566,13 +1589,8 @@ int chfpe_response_2d_range(chfpe_ctx *c, const chfpe_optical *A, const chfpe_op
     }
     // V = B^x U
     launch_perturb<double>(c, c->u, c->y, c->gB);
-    for (int64_t j2 = 0; j2 < n_t2; ++j2) {
-      if (j2 > 0) {
-        rc = rk4(c, c->y, stride2, dt);
-        if (rc) return rc;
-      }
-      observe_to(c, c->y, c->rbuf + j2 * n_t1 + j1);
-    }
+    rc = sample(c, n_t2, stride2, dt, c->rbuf + j1, n_t1);
+    if (rc) return rc;
   }
   HIPCHK(c, hipMemcpyAsync(R, c->rbuf, n * sizeof(double), hipMemcpyDeviceToHost, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
@@ -1625,13 +1643,8 @@ int chfpe_response_3d(chfpe_ctx *c, const chfpe_optical *A, const chfpe_optical 
     if (rc) return rc;
     launch_perturb<double>(c, c->y, c->xa, c->gC);
     std::swap(c->y, c->xa);  // the excited state becomes the propagated one
-    for (int64_t j3 = 0; j3 < n_t3; ++j3) {
-      if (j3 > 0) {
-        rc = rk4(c, c->y, stride3, dt);
-        if (rc) return rc;
-      }
-      observe_to(c, c->y, c->rbuf + j3 * n_t1 + j1);
-    }
+    rc = sample(c, n_t3, stride3, dt, c->rbuf + j1, n_t1);
+    if (rc) return rc;
   }
   HIPCHK(c, hipMemcpyAsync(R, c->rbuf, n * sizeof(double), hipMemcpyDeviceToHost, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));

@@ -12,6 +12,7 @@
 
 #include "chfpe.h"
 #include "kernels.h"
+#include "one.h"
 #include "wave.h"
 
 namespace chfpe {
@@ -71,6 +72,8 @@ struct Launch {
   int hwave_nb = 0;
   int pcube_threads = 0, pcube_nb1 = 0;
   size_t pcube_lds = 0;
+  // one mode: whole propagations by one workgroup per state (k_one)
+  bool one = false;
   int qa_threads = 0, qf_threads = 0, qx_threads = 0;
   size_t qa_lds = 0, qf_lds = 0;
   int qa_nmax = 48, qf_nmax = 48, qx_nmax = 48;
@@ -121,6 +124,7 @@ struct chfpe_ctx {
   bool closure_on = false; // right-hand sides use the closure stencil weights (tb.clos)
   bool use_graphs = true;
   bool allow_pcube = true;  // three modes: k_pcube where the p block fits it
+  bool allow_one = true;    // one mode: k_one where the state fits it
   // kernel timing
   int timing_every = 0;
   long long step_counter = 0;
@@ -150,6 +154,19 @@ inline size_t pcube_lds_bytes(const Derived &d, size_t tsize, int pad, bool stre
     return (kPCubeCF + 2 * (size_t)pcube_s_planes(nb1) * rows +
             (size_t)pcube_s_dlds((int)tsize, nb1) * d.Np[1] * pcube_n3(d)) * tsize;
   return ((size_t)d.P + 2 * (size_t)pcube_planes(nb1) * rows + (size_t)d.Np[0]) * tsize;  // + the p_1 table
+}
+
+// LDS values of a k_one workgroup.
+inline size_t one_lds_vals(const Derived &d) {
+  // (the reads ahead of a line may run past the last array, into the tables)
+  static_assert(kOnePF * one_rs(kMaxAxis) <= kOneTables, "reads ahead stay in the allocation");
+  const int n = std::max(d.Nq[0], d.Np[0]);
+  return (size_t)2 * d.ne * n * one_rs(one_bucket(n)) + kOneTables;
+}
+// k_one takes the one-mode grids that fit its registers and LDS.
+inline bool one_shape_ok(const Derived &d) {
+  return d.M == 1 && !d.hermite && d.ne <= kOneMaxElements &&
+         one_fits(sizeof(double), one_bucket(std::max(d.Nq[0], d.Np[0])), one_ne(d.ne));
 }
 
 // Waves of a k_pwave workgroup.
