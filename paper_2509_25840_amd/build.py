@@ -13,7 +13,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 # longest compilations first
 UNITS = ("launch_qpass_f64", "launch_pblock", "launch_pwave", "launch_pcube", "launch_hermite", "launch_qpass_f32",
-         "launch_one", "chfpe")
+         "launch_qcube", "launch_one", "chfpe")
 LIB = os.path.join(HERE, "libchfpe.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

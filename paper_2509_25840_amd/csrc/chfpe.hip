@@ -568,6 +568,20 @@ bool use_pcube(const chfpe_ctx *c) {
   return !pblock_ok || (d.M == 3 && c->allow_pcube);
 }
 
+// One pass over all q axes (k_qcube) for cubes of 8, 12 or 16 points, whose tile
+// fits a workgroup's registers: it moves four states a stage where the two
+// passes move seven (16^6, eight FP32 states 7.3 -> 4.9 ms a stage; 12^6 FP64
+// 0.316 -> 0.238).  Ragged axes measured no gain, and a closure's weights spill
+// registers: those keep the two passes.  The p block must hold whole 16-byte
+// vectors of both types in use.
+bool use_qcube(const chfpe_ctx *c, long long nbat) {
+  const Derived &d = c->d;
+  const int n = d.Nq[0], vec = d.prec == CHFPE_FP32 ? 4 : 2;
+  const int run = qcube_c(sizeof(double));  // the shorter run: more tasks
+  return c->allow_qcube && (n == 8 || n == 12 || n == 16) && d.Nq[1] == n && d.Nq[2] == n && d.P % vec == 0 &&
+         grid_items((long long)d.ne * ((d.P + run - 1) / run) * nbat, n * n * kQcParts) <= kMaxGridItems;
+}
+
 // Choose tile shapes.  Returns false when a k_qpass launch over every state
 // of the largest batch would exceed one dispatch (the k_pblock shape always
 // fits: derive() checked it).
@@ -693,6 +707,7 @@ bool plan(chfpe_ctx *c) {
       ln.qf_two = false;
       plan_one(c, 0, (d.Q / d.Nq[0]) * d.P, {}, ln.qf, ln.qf_threads, ln.qf_nmax);
       ln.qf_lds = 0;
+      ln.qcube = use_qcube(c, nbat);
     } else {
       ln.has_qa = false;
       ln.qf_two = true;
@@ -828,6 +843,11 @@ void launch_stage(chfpe_ctx *c, const Batch &b, const T *X, T *t, const T *y, T 
   } else {
     TimedScope ts(c, K_PBLOCK, b.g.nbatch, sizeof(T));
     launch_pblock_t<T, T, false>(c, b, X, t, nullptr);
+  }
+  if (ln.qcube && !c->closure_on) {
+    TimedScope ts(c, kind, b.g.nbatch, sizeof(T));
+    launch_qcube<T>(c, b, X, t, y, xo, cst, EPI);
+    return;
   }
   if (ln.has_qa) {
     TimedScope ts(c, K_QACC, b.g.nbatch, sizeof(T));
@@ -1379,6 +1399,7 @@ int chfpe_setup(const chfpe_params *p, void *dev_workspace, size_t ws_bytes, voi
   if (const char *v = std::getenv("CHFPE_TUNE_HC_KTILE")) c->tune_hc_ktile = std::atoi(v);
   if (const char *v = std::getenv("CHFPE_NO_GRAPH")) c->use_graphs = std::atoi(v) == 0;
   if (const char *v = std::getenv("CHFPE_PCUBE")) c->allow_pcube = std::atoi(v) != 0;
+  if (const char *v = std::getenv("CHFPE_QCUBE")) c->allow_qcube = std::atoi(v) != 0;
   if (const char *v = std::getenv("CHFPE_ONE")) c->allow_one = std::atoi(v) != 0;
   std::vector<double> F, Vp, pm, pg, sq, sp, wp, cc, tc, damp;
   std::vector<int> up, dn;

@@ -13,6 +13,7 @@
 #include "chfpe.h"
 #include "kernels.h"
 #include "one.h"
+#include "qcube.h"
 #include "wave.h"
 
 namespace chfpe {
@@ -64,6 +65,8 @@ struct Launch {
   bool pwave = false;  // the streamed form is k_pwave (p axes of at most 24 points)
   int pwave_nb = 0;
   PCube pcb{};
+  // three modes: every q derivative and the stage update in one pass (k_qcube)
+  bool qcube = false;
   // Hermite basis: k_hcube over the q cube of each (branch, element, k)
   bool hcube = false, hcube_split = false;
   PCube hcb{};
@@ -124,6 +127,7 @@ struct chfpe_ctx {
   bool closure_on = false; // right-hand sides use the closure stencil weights (tb.clos)
   bool use_graphs = true;
   bool allow_pcube = true;  // three modes: k_pcube where the p block fits it
+  bool allow_qcube = true;  // three modes: k_qcube where the q cube fits it
   bool allow_one = true;    // one mode: k_one where the state fits it
   // kernel timing
   int timing_every = 0;
@@ -159,7 +163,7 @@ inline size_t pcube_lds_bytes(const Derived &d, size_t tsize, int pad, bool stre
 // LDS values of a k_one workgroup.
 inline size_t one_lds_vals(const Derived &d) {
   // (the reads ahead of a line may run past the last array, into the tables)
-  static_assert(kOnePF * one_rs(kMaxAxis) <= kOneTables, "reads ahead stay in the allocation");
+  static_assert(kStreamPF * one_rs(kMaxAxis) <= kOneTables, "reads ahead stay in the allocation");
   const int n = std::max(d.Nq[0], d.Np[0]);
   return (size_t)2 * d.ne * n * one_rs(one_bucket(n)) + kOneTables;
 }

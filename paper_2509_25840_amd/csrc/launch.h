@@ -16,6 +16,9 @@ void launch_pwave(chfpe_ctx *c, const Batch &b, const T *X, TO *out, const doubl
 template <typename T, typename TO, bool TWO, int EPI, int FA, int FB>
 void launch_q_t(chfpe_ctx *c, const Batch &b, const QPass &qp, int threads, size_t lds, int nmax, const T *X,
                 TO *Tacc, const TO *y, TO *xo, const double *grad, double cst);
+// k_qcube: every q derivative of X added to Tacc, and the stage update epi.
+template <typename T>
+void launch_qcube(chfpe_ctx *c, const Batch &b, const T *X, const T *Tacc, const T *y, T *xo, double cst, int epi);
 // Hermite basis: the right-hand side of X and the stage update (EPI,
 // coefficient cst) over every (branch, element, k).
 template <typename T, int EPI>

@@ -15,7 +15,7 @@
 // workgroup (FP64, fixed order).
 #pragma once
 
-#include "kernels.h"
+#include "wave.h"
 
 namespace chfpe {
 
@@ -42,68 +42,6 @@ constexpr bool one_fits(const int tsize, const int nb, const int ne) {
 }
 constexpr int one_ne(const int ne) { return ne <= 2 ? ne : ne <= 4 ? 4 : kOneMaxElements; }
 constexpr int one_cpt(const int nb) { return nb <= 16 ? 1 : nb <= 32 ? 2 : 3; }
-
-// Compact derivative, over cb (see wave_rhs in wave.h), of a line of n <= NB
-// values (n uniform over the wave) in an LDS column, by one lane.  Streamed:
-// a forward result overwrites its value once the sweep's window has read it,
-// and the back substitution overwrites it in turn, so that few registers hold
-// the line.  Reads run kOnePF positions ahead (and may touch that many rows
-// past the array).  Positions go in blocks of eight with no branch inside but
-// in the block the line ends in: with one per position, a step waits for its
-// five dependent instructions (100 cycles instead of 35).
-constexpr int kOnePF = 4;
-template <typename T, int NB>
-__device__ __forceinline__ void one_line(T *G, const int n) {
-  constexpr int RS = one_rs(NB), PF = kOnePF, BL = 8;
-  static_assert(NB % BL == 0, "whole blocks");
-  T f[PF + 1];  // f_i .. f_{i + PF}; zero past the line
-#pragma unroll
-  for (int j = 0; j < PF; ++j) f[j] = G[j * RS];  // lines have at least five values
-  T fm1 = T(0), fm2 = T(0), d = T(0);
-  auto forward = [&](const int i) {
-    const T nx = i + PF < NB ? G[(i + PF < NB ? i + PF : 0) * RS] : T(0);
-    f[PF] = i + PF < n ? nx : T(0);
-    const T r = fma_t(T(28), f[1] - fm1, f[2] - fm2);
-    d = i == 0 ? r : fma_t(T(-kThomas.inv[i] / 3.0), d, r * T(kThomas.inv[i]));
-    G[i * RS] = d;
-    fm2 = fm1;
-    fm1 = f[0];
-#pragma unroll
-    for (int j = 0; j < PF; ++j) f[j] = f[j + 1];
-  };
-#pragma unroll
-  for (int i0 = 0; i0 < NB; i0 += BL) {
-    if (i0 + BL <= n) {
-#pragma unroll
-      for (int i = i0; i < i0 + BL; ++i) forward(i);
-    } else if (i0 < n) {
-#pragma unroll
-      for (int i = i0; i < i0 + BL - 1; ++i)
-        if (i < n) forward(i);
-    }
-  }
-  T x = d, v[PF + 1];  // d_i .. d_{i - PF}
-#pragma unroll
-  for (int j = 0; j < PF; ++j) v[j] = G[(n - 2 - j) * RS];
-  auto backward = [&](const int i) {
-    v[PF] = G[(i >= PF ? i - PF : 0) * RS];
-    x = v[0] - T(kThomas.cp[i]) * x;
-    G[i * RS] = x;
-#pragma unroll
-    for (int j = 0; j < PF; ++j) v[j] = v[j + 1];
-  };
-#pragma unroll
-  for (int i0 = NB - BL; i0 >= 0; i0 -= BL) {
-    if (i0 + BL <= n - 1) {
-#pragma unroll
-      for (int i = i0 + BL - 1; i >= i0; --i) backward(i);
-    } else if (i0 < n - 1) {
-#pragma unroll
-      for (int i = i0 + BL - 2; i >= i0; --i)
-        if (i < n - 1) backward(i);
-    }
-  }
-}
 
 template <typename T, int NB, int NE>
 __global__ void __launch_bounds__(kOneThreads)
@@ -185,7 +123,7 @@ k_one(const Geom g, const Tabs tb, const OneArgs a, T *__restrict__ states, cons
           const int l = (ql ? v : v - wq) * 64 + lane;
           const int len = ql ? a.Np : a.Nq;  // lines per element
           const int e = l / len;
-          if (l < (ql ? nql : npl)) one_line<T, NB>((ql ? Z : Y) + e * arr + (l - e * len), ql ? a.Nq : a.Np);
+          if (l < (ql ? nql : npl)) stream_line<T, NB>((ql ? Z : Y) + e * arr + (l - e * len), RS, ql ? a.Nq : a.Np);
         }
         __syncthreads();
 #pragma unroll

@@ -114,6 +114,69 @@ __device__ __forceinline__ void wave_line(T *G, const int stride, const int n, c
   }
 }
 
+// Compact derivative, over cb (see wave_rhs), of a line of n <= NB values (n
+// uniform over the wave) in LDS by one lane.  Streamed:
+// a forward result overwrites its value once the sweep's window has read it,
+// and the back substitution overwrites it in turn, so that few registers hold
+// the line.  Reads run kStreamPF positions ahead (and may touch that many rows
+// past the array).  Positions go in blocks of eight with no branch inside but
+// in the block the line ends in: with one per position, a step waits for its
+// five dependent instructions (100 cycles instead of 35).
+constexpr int kStreamPF = 4;
+template <typename T, int NB>
+__device__ __forceinline__ void stream_line(T *G, const int stride, const int n) {
+  constexpr int PF = kStreamPF, BL = 8;
+  static_assert(NB % BL == 0, "whole blocks");
+  T f[PF + 1];  // f_i .. f_{i + PF}; zero past the line
+#pragma unroll
+  for (int j = 0; j < PF; ++j) f[j] = G[j * stride];  // lines have at least five values
+  T fm1 = T(0), fm2 = T(0), d = T(0);
+  auto forward = [&](const int i) {
+    const T nx = i + PF < NB ? G[(i + PF < NB ? i + PF : 0) * stride] : T(0);
+    f[PF] = i + PF < n ? nx : T(0);
+    const T r = fma_t(T(28), f[1] - fm1, f[2] - fm2);
+    d = i == 0 ? r : fma_t(T(-kThomas.inv[i] / 3.0), d, r * T(kThomas.inv[i]));
+    G[i * stride] = d;
+    fm2 = fm1;
+    fm1 = f[0];
+#pragma unroll
+    for (int j = 0; j < PF; ++j) f[j] = f[j + 1];
+  };
+#pragma unroll
+  for (int i0 = 0; i0 < NB; i0 += BL) {
+    if (i0 + BL <= n) {
+#pragma unroll
+      for (int i = i0; i < i0 + BL; ++i) forward(i);
+    } else if (i0 < n) {
+#pragma unroll
+      for (int i = i0; i < i0 + BL - 1; ++i)
+        if (i < n) forward(i);
+    }
+  }
+  asm volatile("" ::: "memory");  // the results are read back, not kept
+  T x = d, v[PF + 1];  // d_i .. d_{i - PF}
+#pragma unroll
+  for (int j = 0; j < PF; ++j) v[j] = G[(n - 2 - j) * stride];
+  auto backward = [&](const int i) {
+    v[PF] = G[(i >= PF ? i - PF : 0) * stride];
+    x = v[0] - T(kThomas.cp[i]) * x;
+    G[i * stride] = x;
+#pragma unroll
+    for (int j = 0; j < PF; ++j) v[j] = v[j + 1];
+  };
+#pragma unroll
+  for (int i0 = NB - BL; i0 >= 0; i0 -= BL) {
+    if (i0 + BL <= n - 1) {
+#pragma unroll
+      for (int i = i0 + BL - 1; i >= i0; --i) backward(i);
+    } else if (i0 < n - 1) {
+#pragma unroll
+      for (int i = i0 + BL - 2; i >= i0; --i)
+        if (i < n - 1) backward(i);
+    }
+  }
+}
+
 // Both in-plane derivatives of a wave's PS planes, in place: GA ([plane][N2]
 // rows of N3) along the rows axis, GB along the columns axis.  GB holds its
 // field transposed ([plane][N3] rows of N2), so that a line of either field

@@ -96,3 +96,32 @@ def test_hwave_matches_the_oracle(pk, Nq, Nh, K):
         e_rk4 = rel_l2(s.get_state(), oh.rk4(w, C, 2, 0.002, T))
     say(f"    rhs {e_rhs:.2e} rk4 {e_rk4:.2e}")
     assert e_rhs < TOL and e_rk4 < TOL
+
+
+@pytest.mark.parametrize("N", [8, 12, 16])
+@pytest.mark.parametrize("Np", [(8, 8, 8), (6, 7, 10), (5, 5, 12)])
+def test_qcube_matches_the_oracle_and_the_two_passes(pk, monkeypatch, N, Np):
+    """k_qcube (q cubes of 8, 12 and 16 points) with p blocks that end in a
+    whole and in a partial run of 64 bytes: the oracle's right-hand side and RK4
+    steps, and the (q_2, q_3) and q_1 passes' FP32 branches (CHFPE_QCUBE=0)."""
+    w = wl.workload("three_mode_24", Nq=[N] * 3, Np=list(Np), K=1)
+    say(f"[k_qcube] q {N} p {Np}")
+    env = orc.boltzmann(w)[0]
+    sm = wl.smooth_state(w, seed=5)
+    W = env[None] * (1.0 + 0.3 * sm / np.abs(sm).max() + 0.05 * wl.noise_state(w, seed=6))
+    R = {}
+    for on in ("1", "0"):
+        monkeypatch.setenv("CHFPE_QCUBE", on)
+        with pk.Solver(pk.params_from_workload(w)) as s:
+            s.set_state(W)
+            s.rhs()
+            e_rhs = rel_l2(s.get_state(), orc.rhs(w, W))
+            s.set_state(W)
+            s.propagate(2, 0.002)
+            e_rk4 = rel_l2(s.get_state(), orc.rk4(w, W, 2, 0.002))
+        assert e_rhs < TOL and e_rk4 < TOL
+        with pk.Solver(pk.params_from_workload(w, precision=pk.CHFPE_FP32, batch=2)) as s:
+            s.equilibrate(4, 0.004)
+            R[on] = s.response_2d(w["A"], w["B"], w["C"], 3, 4, 1, 2, 0.004)
+    say(f"    rhs {e_rhs:.2e} rk4 {e_rk4:.2e} FP32 branches {rel_l2(R['1'], R['0']):.2e}")
+    assert rel_l2(R["1"], R["0"]) < 1e-4
