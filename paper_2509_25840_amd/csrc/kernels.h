@@ -1357,11 +1357,20 @@ k_qpass(const Geom g, const Tabs tb, const QPass qp, const T *__restrict__ X, TO
   const T *Xb = X + (long long)br * g.ne * g.E;
 
   // element i of this thread's a-line: uniform pointer (element base plus
-  // i strides) with the thread's 32-bit offset lrel
+  // i strides) with a 32-bit offset per thread.  No load is under a branch
+  // (it would be waited for where the branch joins): threads past the tile
+  // and points past the line read the last position's value.
+  const int lload = rel + (TWO ? min(jb, qp.Nb - 1) * qp.sb : 0) + min(c, pcn - 1);
   T f[NMAX];
+  if (Na == NMAX) {
 #pragma unroll
-  for (int i = 0; i < NMAX; ++i)
-    f[i] = (active && i < Na) ? at_u32(X + ebase + (long long)i * qp.sa, lrel) : T(0);
+    for (int i = 0; i < NMAX; ++i) f[i] = at_u32(X + ebase + (long long)i * qp.sa, lload);
+  } else {
+#pragma unroll
+    for (int i = 0; i < NMAX; ++i) f[i] = at_u32(X + ebase + (long long)min(i, Na - 1) * qp.sa, lload);
+#pragma unroll
+    for (int i = 0; i < NMAX; ++i) f[i] = i < Na ? f[i] : T(0);
+  }
 
   // LDS tile [ja][jb][c] with row stride (Nb + 1) * pc: the pad keeps the
   // b-line reads of different ja in different banks
@@ -1381,7 +1390,9 @@ k_qpass(const Geom g, const Tabs tb, const QPass qp, const T *__restrict__ X, TO
     if (c < pcn && ja < Na) {
       T h[NMAX];
 #pragma unroll
-      for (int i = 0; i < NMAX; ++i) h[i] = (i < Nb) ? lds[ja * rs + i * pc + c] : T(0);
+      for (int i = 0; i < NMAX; ++i) h[i] = lds[ja * rs + min(i, Nb - 1) * pc + c];
+#pragma unroll
+      for (int i = 0; i < NMAX; ++i) h[i] = i < Nb ? h[i] : T(0);
       compact_line<T, NMAX, CLOS>(h, Nb, T(qp.ca_b), T(qp.cb_b), CLOS ? tb.clos + qp.b * 2 * kClosRows * kTab : nullptr);
 #pragma unroll
       for (int i = 0; i < NMAX; ++i)
@@ -1415,15 +1426,16 @@ k_qpass(const Geom g, const Tabs tb, const QPass qp, const T *__restrict__ X, TO
     kb = T(-tb.pm[s * kTab + (pix0 / g.PS[s]) % g.Np[s]]);
   }
   const T cs = T(cst);
-  if ((EPI == EPI_ACC || EPI == EPI_H1) && Na == NMAX) {
-    // Full lines (one uniform branch): the epilogue's loads go in groups of
-    // four points, issued one group ahead.  In the per-point form below each
-    // point's load sits under an "i < Na" branch and is waited for before
-    // the next point's load is issued.  Each group's offset passes through
-    // an empty asm statement, which keeps its loads after the previous
-    // group's stores.  (The stage-final passes that read y or xo as well run
-    // at the device's streaming rate either way; grouped, they measured 1%
-    // slower.)
+  // The epilogue's loads go in groups of four points, issued one group ahead;
+  // each group's offset passes through an empty asm statement, which keeps its
+  // loads after the previous group's stores.  With a load per point under its
+  // "i < Na" branch, each is waited for before the next point's is issued:
+  // two-axis passes of 32^4 (64 states) H2 5.05 -> 4.02 ms in FP64 and 4.30 ->
+  // 2.49 in FP32 (there also with its tile sized for FP32, two workgroups per
+  // CU), 17 x 19 x 14 points 0.40 -> 0.28 ms, 24^6 FP32 7.4 -> 5.3 ms; large
+  // one-axis passes stream at 5.2 TB/s either way.
+  auto update = [&](auto FULL_) {
+    constexpr bool FULL = decltype(FULL_)::value;
     constexpr int GE = 4;  // NMAX is a multiple of 4
     T ct[GE], cy[GE];
     auto load_e = [&](const int i0, T (&tv)[GE], T (&yv)[GE]) {
@@ -1431,7 +1443,7 @@ k_qpass(const Geom g, const Tabs tb, const QPass qp, const T *__restrict__ X, TO
       asm volatile("" : "+v"(b));
 #pragma unroll
       for (int k = 0; k < GE; ++k) {
-        const long long ui = ebase + (long long)(i0 + k) * qp.sa;
+        const long long ui = ebase + (long long)(FULL ? i0 + k : min(i0 + k, Na - 1)) * qp.sa;
         tv[k] = T(at_u32(Tacc + ui, b));
         yv[k] = EPI == EPI_H2 ? T(at_u32(y + ui, b)) : EPI == EPI_H4 ? T(at_u32(xo + ui, b)) : T(0);
       }
@@ -1444,6 +1456,7 @@ k_qpass(const Geom g, const Tabs tb, const QPass qp, const T *__restrict__ X, TO
 #pragma unroll
       for (int k = 0; k < GE; ++k) {
         const int i = i0 + k;
+        if (!FULL && i >= Na) break;  // uniform
         T kv = ka * d[i];
         if (TWO) kv += kb * lds[i * rs + jb * qp.pc + c];
         const long long ui = ebase + (long long)i * qp.sa;
@@ -1468,31 +1481,11 @@ k_qpass(const Geom g, const Tabs tb, const QPass qp, const T *__restrict__ X, TO
         }
       }
     }
-    return;
-  }
-#pragma unroll
-  for (int i = 0; i < NMAX; ++i) {
-    if (i < Na) {
-      T kv = ka * d[i];
-      if (TWO) kv += kb * lds[i * rs + jb * qp.pc + c];
-      const long long ui = ebase + (long long)i * qp.sa;  // uniform part of the index
-      TO &tacc = at_u32(Tacc + ui, lrel);
-      if (EPI == EPI_ACC) {
-        tacc = TO(T(tacc) + kv);
-      } else {
-        kv += T(tacc);
-        TO &xov = at_u32(xo + ui, lrel);
-        if (EPI == EPI_OUT)
-          xov = TO(kv);
-        else if (EPI == EPI_H1)
-          xov = TO(f[i] + cs * kv);
-        else if (EPI == EPI_H2)
-          xov = TO(T(at_u32(y + ui, lrel)) + cs * kv);
-        else  // EPI_H4
-          xov = TO(T(xov) + cs * kv);
-      }
-    }
-  }
+  };
+  if (Na == NMAX)
+    update(std::true_type{});
+  else
+    update(std::false_type{});
 }
 
 // ---------------------------------------------------------------------------

@@ -26,6 +26,7 @@ void launch_q_n(chfpe_ctx *c, const Batch &b, const QPass &qp, int threads, size
 template <typename T, typename TO, bool TWO, int EPI, int FA, int FB>
 void launch_q_t(chfpe_ctx *c, const Batch &b, const QPass &qp, int threads, size_t lds, int nmax, const T *X,
                 TO *Tacc, const TO *y, TO *xo, const double *grad, double cst) {
+  lds = lds / sizeof(double) * sizeof(T);  // the plan's tile is one of doubles
 #define CHFPE_QN(N) launch_q_n<T, TO, N, TWO, EPI, FA, FB>(c, b, qp, threads, lds, X, Tacc, y, xo, grad, cst)
   switch (nmax) {
     case 8: CHFPE_QN(8); break;
