@@ -728,6 +728,22 @@ bool plan(chfpe_ctx *c) {
     ln.has_qx = true;
     plan_one(c, M + 0, plane, {0, 1, 2}, ln.qx, ln.qx_threads, ln.qx_nmax);
   }
+  // two modes: k_pwave2 where a wave's lines hold the p axes and no k_pblock or
+  // k_pcube form is asked for by name
+  ln.pwave2 = false;
+  if (M == 2 && std::max(d.Np[0], d.Np[1]) <= 32 && c->allow_pwave2 && c->tune_pb_nb <= 0 && c->tune_pb_split < 0 &&
+      c->tune_pb_run <= 0 && c->tune_pc_stream < 0) {
+    PCube &w2 = ln.pw2;
+    ln.pwave2_nb = nmax_bucket(std::max(d.Np[0], d.Np[1]));
+    w2.N1 = 1;
+    w2.N2 = d.Np[0];
+    w2.N3 = d.Np[1];
+    w2.plane = w2.N2 * w2.N3;
+    w2.ntasks = (int)std::min<long long>((long long)d.ne * d.Q, 1LL << 30);
+    w2.nblk = pwave2_nblk(w2.ntasks);
+    ln.pwave2 = grid_items(((long long)w2.ntasks * nbat + kPWave2Waves - 1) / kPWave2Waves, 64 * kPWave2Waves) <=
+                kMaxGridItems;
+  }
   auto fits = [&](const QPass &q, int thr) { return grid_items((long long)q.ntasks * nbat, thr) <= kMaxGridItems; };
   return fits(ln.qf, ln.qf_threads) && (!ln.has_qa || fits(ln.qa, ln.qa_threads)) &&
          (!ln.has_qx || fits(ln.qx, ln.qx_threads)) &&
@@ -805,6 +821,9 @@ Batch batch_of(const chfpe_ctx *c, int nb) {
   b.pcb = c->ln.pcb;
   b.pcb.ntasks *= nb;
   b.pcb.nblk = pad8(b.pcb.ntasks);
+  b.pw2 = c->ln.pw2;
+  b.pw2.ntasks *= nb;
+  b.pw2.nblk = pwave2_nblk(b.pw2.ntasks);
   b.hcb = c->ln.hcb;
   b.hcb.ntasks *= nb;
   b.hcb.nblk = hcube_nblk(b.hcb.ntasks, b.hcb.chunk);
@@ -834,7 +853,10 @@ void launch_stage(chfpe_ctx *c, const Batch &b, const T *X, T *t, const T *y, T 
       launch_hcube<T, EPI>(c, b, X, y, xo, cst);
     return;
   }
-  if (ln.pcube) {
+  if (ln.pwave2) {
+    TimedScope ts(c, ln.pcube ? K_PCUBE : K_PBLOCK, b.g.nbatch, sizeof(T));
+    launch_pwave2<T, T, false>(c, b, X, t, nullptr);
+  } else if (ln.pcube) {
     TimedScope ts(c, K_PCUBE, b.g.nbatch, sizeof(T));
     if (ln.pwave)
       launch_pwave<T, T, false>(c, b, X, t, nullptr);
@@ -873,6 +895,10 @@ void launch_perturb(chfpe_ctx *c, const double *W, TO *out, const double *grad) 
   const Batch b = batch_of(c, 1);
   if (c->ln.hcube) {  // Hermite basis: a local raising of k, no derivative
     hipLaunchKernelGGL((k_hperturb<TO>), dim3(2048), dim3(256), 0, c->stream, b.g, W, out, grad);
+    return;
+  }
+  if (c->ln.pwave2) {
+    launch_pwave2<double, TO, true>(c, b, W, out, grad);
     return;
   }
   if (c->ln.pcube) {
@@ -1399,6 +1425,7 @@ int chfpe_setup(const chfpe_params *p, void *dev_workspace, size_t ws_bytes, voi
   if (const char *v = std::getenv("CHFPE_TUNE_HC_KTILE")) c->tune_hc_ktile = std::atoi(v);
   if (const char *v = std::getenv("CHFPE_NO_GRAPH")) c->use_graphs = std::atoi(v) == 0;
   if (const char *v = std::getenv("CHFPE_PCUBE")) c->allow_pcube = std::atoi(v) != 0;
+  if (const char *v = std::getenv("CHFPE_PWAVE2")) c->allow_pwave2 = std::atoi(v) != 0;
   if (const char *v = std::getenv("CHFPE_QCUBE")) c->allow_qcube = std::atoi(v) != 0;
   if (const char *v = std::getenv("CHFPE_ONE")) c->allow_one = std::atoi(v) != 0;
   std::vector<double> F, Vp, pm, pg, sq, sp, wp, cc, tc, damp;
@@ -1899,7 +1926,8 @@ int chfpe_autotune(chfpe_ctx *c, int32_t n_steps) {
     c->tune_q_pc = t.q_pc;
     c->tune_pb_run = t.pb_run;
     if (!plan(c)) return CHFPE_OK;  // too large a launch for one dispatch: not a candidate
-    const std::vector<int> eff = {c->ln.pb.nb, c->ln.pb.split, c->ln.qf.pc, c->ln.qa.pc, c->ln.pb.run};
+    const std::vector<int> eff = {c->ln.pb.nb, c->ln.pb.split, c->ln.qf.pc, c->ln.qa.pc, c->ln.pb.run,
+                                  c->ln.pwave2};
     for (const auto &s : seen)
       if (s == eff) return CHFPE_OK;  // same launches as a shape already timed
     seen.push_back(eff);
@@ -1911,9 +1939,11 @@ int chfpe_autotune(chfpe_ctx *c, int32_t n_steps) {
     }
     return CHFPE_OK;
   };
-  // k_pblock shapes first (q tiles automatic), then q tiles with the best,
-  // then the k_pblock task order
+  // the starting shapes (two modes: k_pwave2 where it takes the p side), then
+  // k_pblock shapes (q tiles automatic), q tiles with the best, and the
+  // k_pblock task order
   std::vector<std::vector<int>> seen;
+  if (trial(TileChoice(best), seen)) return restore(fail(c, CHFPE_EDEVICE, "autotune step failed"));
   for (int split : {1, 0})
     for (int nb : {1, 2, 4, 8})
       if (trial(TileChoice{nb, split, best.q_pc, best.pb_run}, seen))

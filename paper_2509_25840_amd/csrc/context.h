@@ -64,6 +64,10 @@ struct Launch {
   bool pcube = false, pcube_split = false, pcube_stream = false;
   bool pwave = false;  // the streamed form is k_pwave (p axes of at most 24 points)
   int pwave_nb = 0;
+  // two modes: the p side by k_pwave2 (p axes of at most 32 points)
+  bool pwave2 = false;
+  int pwave2_nb = 0;
+  PCube pw2{};
   PCube pcb{};
   // three modes: every q derivative and the stage update in one pass (k_qcube)
   bool qcube = false;
@@ -85,6 +89,9 @@ struct Launch {
 inline int pad8(int n) { return (n + 7) / 8 * 8; }
 // k_hcube grid: a multiple of 8 chunks when the tasks go to the XCDs in chunks
 inline int hcube_nblk(int ntasks, int chunk) { return chunk > 0 ? (ntasks + 8 * chunk - 1) / (8 * chunk) * (8 * chunk) : pad8(ntasks); }
+
+// k_pwave2 grid: a wave per task
+inline int pwave2_nblk(int ntasks) { return pad8((ntasks + kPWave2Waves - 1) / kPWave2Waves); }
 
 }  // namespace chfpe
 
@@ -127,6 +134,7 @@ struct chfpe_ctx {
   bool closure_on = false; // right-hand sides use the closure stencil weights (tb.clos)
   bool use_graphs = true;
   bool allow_pcube = true;  // three modes: k_pcube where the p block fits it
+  bool allow_pwave2 = true; // two modes: k_pwave2 where a wave's lines hold the p axes
   bool allow_qcube = true;  // three modes: k_qcube where the q cube fits it
   bool allow_one = true;    // one mode: k_one where the state fits it
   // kernel timing
@@ -200,7 +208,7 @@ void allow_lds(K kern, size_t bytes) {
 struct Batch {
   Geom g;
   PBlock pb;
-  PCube pcb, hcb;
+  PCube pcb, pw2, hcb;
   QPass qa, qf, qx;
 };
 

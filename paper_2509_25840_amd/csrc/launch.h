@@ -12,6 +12,8 @@ template <typename T, typename TO, bool PERTURB>
 void launch_pcube_t(chfpe_ctx *c, const Batch &b, const T *X, TO *out, const double *grad);
 template <typename T, typename TO, bool PERTURB>
 void launch_pwave(chfpe_ctx *c, const Batch &b, const T *X, TO *out, const double *grad);
+template <typename T, typename TO, bool PERTURB>
+void launch_pwave2(chfpe_ctx *c, const Batch &b, const T *X, TO *out, const double *grad);
 // k_qpass over the axes of qp.
 template <typename T, typename TO, bool TWO, int EPI, int FA, int FB>
 void launch_q_t(chfpe_ctx *c, const Batch &b, const QPass &qp, int threads, size_t lds, int nmax, const T *X,

@@ -50,7 +50,47 @@ void launch_pwave(chfpe_ctx *c, const Batch &b, const T *X, TO *out, const doubl
   }
 }
 
-#define CHFPE_INST(T, TO, P) template void launch_pwave<T, TO, P>(chfpe_ctx *, const Batch &, const T *, TO *, const double *);
+// k_pwave2 (two modes): a square plane of NB points on both axes (NVR = 0), or
+// any plane of at most 64 NVR points with axes of at most NB points.
+template <typename T, typename TO, int NB, int NVR, bool PERTURB>
+void launch_pwave2_k(chfpe_ctx *c, const Batch &b, const T *X, TO *out, const double *grad) {
+  const size_t lds = sizeof(T) * pwave2_lds_vals(NB, b.pw2.N2, b.pw2.N3, c->closure_on);
+  auto go = [&](auto kern) {
+    allow_lds(kern, lds);
+    hipLaunchKernelGGL(kern, dim3(b.pw2.nblk), dim3(64 * kPWave2Waves), lds, c->stream, b.g, c->tb, b.pw2, X, out,
+                       grad);
+  };
+  if constexpr (kClosureBuilt<T, TO, NB>) {
+    if (c->closure_on) return go(k_pwave2<T, TO, NB, NVR, PERTURB, true>);
+  }
+  go(k_pwave2<T, TO, NB, NVR, PERTURB>);
+}
+
+template <typename T, typename TO, int NB, bool PERTURB>
+void launch_pwave2_n(chfpe_ctx *c, const Batch &b, const T *X, TO *out, const double *grad) {
+  constexpr int full = wave_nv(NB, 1, 1);
+  if (b.pw2.N2 == NB && b.pw2.N3 == NB) return launch_pwave2_k<T, TO, NB, 0, PERTURB>(c, b, X, out, grad);
+  if constexpr (full >= 4) {
+    constexpr int part = (full * 5 + 7) / 8;  // planes well below NB x NB: fewer registers
+    if (b.pw2.plane <= 64 * part) return launch_pwave2_k<T, TO, NB, part, PERTURB>(c, b, X, out, grad);
+  }
+  launch_pwave2_k<T, TO, NB, full, PERTURB>(c, b, X, out, grad);
+}
+
+template <typename T, typename TO, bool PERTURB>
+void launch_pwave2(chfpe_ctx *c, const Batch &b, const T *X, TO *out, const double *grad) {
+  switch (c->ln.pwave2_nb) {
+    case 8: launch_pwave2_n<T, TO, 8, PERTURB>(c, b, X, out, grad); break;
+    case 12: launch_pwave2_n<T, TO, 12, PERTURB>(c, b, X, out, grad); break;
+    case 16: launch_pwave2_n<T, TO, 16, PERTURB>(c, b, X, out, grad); break;
+    case 24: launch_pwave2_n<T, TO, 24, PERTURB>(c, b, X, out, grad); break;
+    default: launch_pwave2_n<T, TO, 32, PERTURB>(c, b, X, out, grad); break;
+  }
+}
+
+#define CHFPE_INST(T, TO, P)                                                                                \
+  template void launch_pwave<T, TO, P>(chfpe_ctx *, const Batch &, const T *, TO *, const double *);        \
+  template void launch_pwave2<T, TO, P>(chfpe_ctx *, const Batch &, const T *, TO *, const double *);
 CHFPE_INST(double, double, false)
 CHFPE_INST(float, float, false)
 CHFPE_INST(double, double, true)

@@ -502,6 +502,177 @@ k_pwave(const Geom g, const Tabs tb, const PCube pc, const T *__restrict__ X, TO
 }
 
 // ---------------------------------------------------------------------------
+// k_pwave2 (two modes): the p side of one q point by one wave
+// ---------------------------------------------------------------------------
+// Same task, inputs and result as k_pblock for two modes, in the wave-plane
+// form: the p block of a task is one (p_1, p_2) plane, a wave takes a task by
+// itself (four consecutive tasks, elements of one q point, per workgroup),
+// and there is no barrier but the one after the grids are in LDS.  Loads of a
+// missing neighbour are of an empty buffer.  Per launch, before (k_pblock:
+// one-value loads and three barriers a task) and after: 32^4 with 64 FP64
+// states 3.58 -> 2.45 ms (4.4 TB/s of algorithmic bytes), 64 FP32 states 2.17
+// -> 1.22 ms; one FP64 state of 32^4 0.054 -> 0.042, 24^4 0.024 -> 0.017,
+// 27 x 28 points 0.072 -> 0.044, 16^4 0.011 -> 0.009 ms.
+constexpr int kPWave2Waves = 4;
+constexpr size_t pwave2_lds_vals(const int nb, const int n1, const int n2, const bool clos) {
+  return 2 * (size_t)kPWave2Waves * (wave_slot(n1, n2, 1) + 16) + 2 * (size_t)nb +
+         (clos ? 2 * (size_t)wave_clos_vals(nb) : 0);
+}
+
+template <typename T, typename TO, int NB, int NVR, bool PERTURB, bool CLOS = false>
+__global__ void __launch_bounds__(64 * kPWave2Waves)
+k_pwave2(const Geom g, const Tabs tb, const PCube pc, const T *__restrict__ X, TO *__restrict__ out,
+         const double *__restrict__ grad) {
+  constexpr bool EXACT = NVR == 0;
+  constexpr int V = wave_vec(sizeof(T), EXACT);
+  constexpr int NV = EXACT ? wave_nv(NB, 1, V) : NVR;
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wg = xcd_task(blockIdx.x, pc.nblk);
+  if (wg * kPWave2Waves >= pc.ntasks) return;
+  const int task = min(wg * kPWave2Waves + w, pc.ntasks - 1);  // (waves past the last task store nothing)
+  const int N2 = EXACT ? NB : pc.N2, N3 = EXACT ? NB : pc.N3;
+  const int plane = EXACT ? NB * NB : pc.plane;
+  const int rs = wave_rs(N2, N3), slot = wave_slot(N2, N3, 1);
+  T *GA = reinterpret_cast<T *>(smem_raw) + 2 * w * (slot + 16), *GB = GA + slot + 16;
+  T *P1 = reinterpret_cast<T *>(smem_raw) + 2 * kPWave2Waves * (slot + 16), *P2 = P1 + NB;
+  T *ctab = P2 + NB;
+  const int ne_all = g.ne * g.nbatch;
+  const int ea = task % ne_all;
+  const int ql = task / ne_all;
+  const int br = ea / g.ne;
+  const int e = ea - br * g.ne;
+  const int Q = g.Q;
+
+  const long long blk = (long long)ql * g.P;
+  const uint32_t bytes = (uint32_t)g.P * (uint32_t)sizeof(T);
+  const T *Xb = X + (long long)br * g.ne * g.E + blk;
+  const Buf bh = make_buf(X + (long long)ea * g.E + blk, bytes);
+  Buf bu[2], bd[2];
+  // fields (times cb, see wave_rhs) and pointwise factors, as in k_pwave
+  T Fv[2], vu[2], vd[2], pwu[2], pwd[2], xs[2];
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    const int up = PERTURB ? -1 : tb.up[e * 3 + s];
+    const int dn = PERTURB ? -1 : tb.dn[e * 3 + s];
+    const double cb = CLOS ? 1.0 : g.dp_cb[s];
+    bu[s] = make_buf(Xb + (long long)max(up, 0) * g.E, up >= 0 ? bytes : 0);
+    bd[s] = make_buf(Xb + (long long)max(dn, 0) * g.E, dn >= 0 ? bytes : 0);
+    if (PERTURB) {
+      const double gr = grad[s * Q + ql];
+      Fv[s] = uniform(T(gr * cb));
+      xs[s] = uniform(T(gr * g.bm[s]));
+      vu[s] = vd[s] = pwu[s] = pwd[s] = T(0);
+    } else {
+      const double vp = tb.VpQ[s * Q + ql];
+      Fv[s] = uniform(T(tb.F[s * Q + ql] * cb));
+      vu[s] = uniform(T(vp * cb));
+      vd[s] = uniform(T(vp * tb.cc[e * 3 + s] * cb));
+      pwd[s] = uniform(T(vp * 0.5 * tb.tc[e * 3 + s]));
+      pwu[s] = uniform(T(vp * g.bm[s]));
+      xs[s] = T(0);
+    }
+  }
+  const T dmp = PERTURB ? T(0) : uniform(T(tb.damp[e]));
+  const int tl = min(tid, NB - 1);
+  const T tp1 = T(tb.pg[tl]), tp2 = T(tb.pg[kTab + tl]);
+
+  constexpr int PER0 = NB / V / wave_gcd(NB / V, 64);
+  constexpr int DR = 64 * V * PER0 / NB;
+  constexpr int PER = EXACT && PER0 < NV ? PER0 : NV;
+  int row[PER], col[PER];
+#pragma unroll
+  for (int m = 0; m < PER; ++m) {
+    const int idx = min(V * (lane + 64 * m), plane - V);
+    row[m] = idx / N3;
+    col[m] = idx - row[m] * N3;
+  }
+  auto at_a = [&](const int m) { return row[m % PER] * rs + col[m % PER] + m / PER * (DR * rs); };
+  auto at_b = [&](const int m) { return col[m % PER] * rs + row[m % PER] + m / PER * DR; };
+  auto mine = [&](const int m) { return (EXACT && V * 64 * (m + 1) <= NB * NB) || V * (lane + 64 * m) < plane; };
+
+  struct In {
+    Vec<T, V> h, u[2], d[2];
+  };
+  auto load = [&](const int m) {
+    In x;
+    uint32_t vo = (uint32_t)(lane + 64 * m) * (uint32_t)(V * sizeof(T));
+    asm volatile("" : "+v"(vo));  // keeps the loads where they are issued (see k_pwave)
+    x.h = buf_load<T, V>(bh, vo, 0);
+    if constexpr (!PERTURB) {
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        x.u[s] = buf_load<T, V>(bu[s], vo, 0);
+        x.d[s] = buf_load<T, V>(bd[s], vo, 0);
+      }
+    }
+    return x;
+  };
+  constexpr int DEPTH = NV < 3 ? NV : 3;
+  In ring[DEPTH];
+#pragma unroll
+  for (int m = 0; m < DEPTH; ++m) ring[m] = load(m);
+  if (tid < NB) {
+    P1[tid] = tp1;
+    P2[tid] = tp2;
+  }
+  if constexpr (CLOS) {
+    for (int v = tid; v < 2 * wave_clos_vals(NB); v += blockDim.x) {
+      const int ax = v / wave_clos_vals(NB), r = v - ax * wave_clos_vals(NB);
+      ctab[v] = T(tb.clos[(g.M + ax) * 2 * kClosRows * kTab + (r / NB) * kTab + r % NB]);
+    }
+  }
+  __syncthreads();
+  T sv[NV][V];
+#pragma unroll
+  for (int m = 0; m < NV; ++m) {
+    const In cur = ring[m % DEPTH];
+    const T p1 = P1[row[m % PER] + m / PER * DR];
+    Vec<T, V> f1, f2;
+#pragma unroll
+    for (int q = 0; q < V; ++q) {
+      const T h = cur.h.v[q], p2 = P2[col[m % PER] + q];
+      T s, a1 = Fv[0] * h, a2 = Fv[1] * h;
+      if constexpr (PERTURB) {
+        s = -(xs[0] * p1 + xs[1] * p2) * h;
+      } else {
+        const T u1 = cur.u[0].v[q], u2 = cur.u[1].v[q], d1 = cur.d[0].v[q], d2 = cur.d[1].v[q];
+        a1 += vd[0] * d1 + vu[0] * u1;
+        a2 += vd[1] * d2 + vu[1] * u2;
+        s = -dmp * h + p1 * (pwd[0] * d1 - pwu[0] * u1) + p2 * (pwd[1] * d2 - pwu[1] * u2);
+      }
+      asm volatile("" : "+v"(s));  // formed here: its inputs are not kept
+      sv[m][q] = s;
+      f1.v[q] = a1;
+      f2.v[q] = a2;
+    }
+    if (m + DEPTH < NV) ring[m % DEPTH] = load(m + DEPTH);
+    if (mine(m)) {
+#pragma unroll
+      for (int q = 0; q < V; ++q) GA[at_a(m) + q] = f1.v[q];
+#pragma unroll
+      for (int q = 0; q < V; ++q) GB[at_b(m) + q * rs] = f2.v[q];
+    }
+  }
+  wave_lds_fence();
+  plane_solve<T, NB, 1, EXACT, CLOS>(GA, GB, lane, N2, N3, rs, slot, ctab, ctab + wave_clos_vals(NB));
+  wave_lds_fence();
+  if (wg * kPWave2Waves + w >= pc.ntasks) return;
+  TO *Oe = out + (long long)ea * g.E + blk;
+#pragma unroll
+  for (int m = 0; m < NV; ++m) {
+    if (!mine(m)) continue;
+    Vec<TO, V> o;
+#pragma unroll
+    for (int q = 0; q < V; ++q) o.v[q] = TO(sv[m][q] + (GA[at_a(m) + q] + GB[at_b(m) + q * rs]));
+    *reinterpret_cast<Vec<TO, V> *>(reinterpret_cast<char *>(Oe) +
+                                    (uint32_t)(V * (lane + 64 * m)) * (uint32_t)sizeof(TO)) = o;
+  }
+}
+
+// ---------------------------------------------------------------------------
 // k_hwave (Hermite basis, two and three modes): a whole RK4 stage of one q cube
 // ---------------------------------------------------------------------------
 // Same task, task order, inputs and result as k_hcube, in the wave-plane form:

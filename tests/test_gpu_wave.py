@@ -1,4 +1,4 @@
-"""The wave-plane kernels (k_pwave, k_hwave) at the edges of their shapes:
+"""The wave-plane kernels (k_pwave, k_pwave2, k_hwave) at the edges of their shapes:
 cubes of every line bucket, ragged blocks whose planes just fill or just pass
 the vectors per lane of a variant, one- and two-plane remainders, and the
 shortest axes, against the FP64 oracles.
@@ -67,6 +67,47 @@ def test_pwave_matches_the_oracle(pk, Np, K):
         e_x = rel_l2(s.get_state(), orc.perturb(w, X3, W))
     say(f"    rhs {e_rhs:.2e} rk4 {e_rk4:.2e} perturb {e_x:.2e}")
     assert e_rhs < TOL and e_rk4 < TOL and e_x < TOL
+
+
+# (p axes, K): squares of every line bucket; planes N1 x N2 that just fill or just
+# pass 64 values per lane slot; task counts that are no multiple of a
+# workgroup's four
+PWAVE2 = [((8, 8), 2), ((12, 12), 1), ((16, 16), 3), ((24, 24), 0), ((32, 32), 1), ((5, 8), 1), ((7, 6), 0), ((9, 12), 2),
+          ((16, 12), 0), ((13, 16), 1), ((24, 16), 1), ((17, 23), 2), ((32, 20), 1), ((25, 26), 0), ((31, 32), 1),
+          ((5, 32), 2), ((29, 5), 1)]
+
+
+@pytest.mark.parametrize("Np,K", PWAVE2, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else f"k{v}")
+def test_pwave2_matches_the_oracle_and_k_pblock(pk, monkeypatch, Np, K):
+    """k_pwave2 (two modes, p axes of up to 32 points): the oracle's right-hand
+    side, RK4 steps and excitation, and k_pblock's FP32 branches
+    (CHFPE_PWAVE2=0)."""
+    w = wl.workload("two_mode_32", Nq=[5, 7], Np=list(Np), K=K)
+    say(f"[k_pwave2] p {Np} K {K}")
+    env = orc.boltzmann(w)[0]
+    sm = wl.smooth_state(w, seed=3)
+    W = env[None] * (1.0 + 0.3 * sm / np.abs(sm).max() + 0.05 * wl.noise_state(w, seed=4))
+    X2 = {"lin": X3["lin"][:2], "quad": [r[:2] for r in X3["quad"][:2]]}
+    R = {}
+    for on in ("1", "0"):
+        monkeypatch.setenv("CHFPE_PWAVE2", on)
+        with pk.Solver(pk.params_from_workload(w)) as s:
+            s.set_state(W)
+            s.rhs()
+            e_rhs = rel_l2(s.get_state(), orc.rhs(w, W))
+            s.set_state(W)
+            s.propagate(2, 0.002)
+            e_rk4 = rel_l2(s.get_state(), orc.rk4(w, W, 2, 0.002))
+            s.set_state(W)
+            s.perturb(X2)
+            e_x = rel_l2(s.get_state(), orc.perturb(w, X2, W))
+        say(f"    rhs {e_rhs:.2e} rk4 {e_rk4:.2e} perturb {e_x:.2e}")
+        assert e_rhs < TOL and e_rk4 < TOL and e_x < TOL
+        with pk.Solver(pk.params_from_workload(w, precision=pk.CHFPE_FP32, batch=3)) as s:
+            s.equilibrate(4, 0.004)
+            R[on] = s.response_2d(w["A"], w["B"], w["C"], 4, 4, 1, 2, 0.004)
+    say(f"    FP32 branches {rel_l2(R['1'], R['0']):.2e}")
+    assert rel_l2(R["1"], R["0"]) < 1e-4
 
 
 # (q axes, Hermite functions, K): as above; two modes take planes N1 x N2 by
