@@ -1279,12 +1279,27 @@ void launch_axis_deriv(hipStream_t st, const double *X, double *Y, const double 
 // Device scratch owned by one closure call (freed on every exit path).
 struct DevScratch {
   std::vector<void *> ptrs;
+  unsigned char *at = nullptr;  // arena: the next pieces come from here
+  size_t left = 0;
   ~DevScratch() {
     for (void *q : ptrs) (void)hipFree(q);
+  }
+  static size_t piece(size_t bytes) { return align_up(std::max<size_t>(bytes, 1), 256); }
+  bool arena(size_t bytes) {  // one allocation for pieces of `bytes` in all (see piece)
+    at = get<unsigned char>(bytes);
+    left = at ? bytes : 0;
+    return at != nullptr;
   }
   template <typename X>
   X *get(size_t n) {
     void *q = nullptr;
+    const size_t p = piece(n * sizeof(X));
+    if (p <= left) {
+      q = at;
+      at += p;
+      left -= p;
+      return static_cast<X *>(q);
+    }
     if (hipMalloc(&q, std::max<size_t>(n, 1) * sizeof(X)) != hipSuccess) return nullptr;
     ptrs.push_back(q);
     return static_cast<X *>(q);
@@ -2183,50 +2198,67 @@ int chfpe_closure_train(const float *feat, int32_t rows, int32_t n_groups, const
       n_groups < 1 || n_steps < 0 || n_steps > 1000000 || adam_t0 < 0 || !(lr > 0.f))
     return fail_g(CHFPE_EINVAL, "invalid arguments");
   if (group_start[0] != 0 || group_start[n_groups] != rows) return fail_g(CHFPE_EINVAL, "groups must cover the rows");
-  std::vector<int> gof(rows);
-  std::vector<long long> goff(n_groups);
-  std::vector<int> boff(n_groups);
+  std::vector<ClosGroup> groups(n_groups);
   long long gtot = 0;
-  int btot = 0;
   for (int q = 0; q < n_groups; ++q) {
-    const int P = group_start[q + 1] - group_start[q];
+    const int i0 = group_start[q], P = group_start[q + 1] - i0;
     if (P < 1) return fail_g(CHFPE_EINVAL, "empty group");
-    goff[q] = gtot;
-    boff[q] = btot;
-    gtot += (long long)P * P;
-    btot += P;
-    for (int r = group_start[q]; r < group_start[q + 1]; ++r) gof[r] = q;
     if (!(ct[2 * q + 1] > 0.0)) return fail_g(CHFPE_EINVAL, "group target norm must be positive");
+    groups[q] = ClosGroup{gtot, i0, P, ct[2 * q], ct[2 * q + 1]};
+    gtot += (long long)P * P;
   }
   hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
+  const int prows = (rows + 15) / 16 * 16;  // whole tiles
   DevScratch ds;
+  const size_t pieces[] = {(size_t)rows * kClosFeat * sizeof(float), (size_t)rows * kClosFeat * sizeof(short),
+                           (size_t)prows * kClosFeat * sizeof(short), n_groups * sizeof(ClosGroup),
+                           gtot * sizeof(double), gtot * sizeof(double), rows * sizeof(double),
+                           n_groups * sizeof(double), 2 * sizeof(ClosState), sizeof(ClosParts), prows * sizeof(float),
+                           prows * sizeof(float), (size_t)prows * kClosHid * sizeof(float), n_steps * sizeof(float)};
+  size_t total = 0;
+  for (const size_t p : pieces) total += DevScratch::piece(p);
+  if (!ds.arena(total)) return fail_g(CHFPE_ENOMEM, "closure train scratch");
   short *dfeat = upload_features(ds, feat, rows, st);
-  int *dgs = ds.get<int>(n_groups + 1), *dgof = ds.get<int>(rows), *dboff = ds.get<int>(n_groups);
-  long long *dgoff = ds.get<long long>(n_groups);
-  double *dG = ds.get<double>(gtot), *db = ds.get<double>(btot), *dct = ds.get<double>(2 * n_groups);
-  float *dp = ds.get<float>(kClosParams), *dm = ds.get<float>(kClosParams), *dv = ds.get<float>(kClosParams);
-  float *dsv = ds.get<float>(rows), *dgsv = ds.get<float>(rows), *dl = ds.get<float>(std::max(1, n_steps));
-  if (!dfeat || !dgs || !dgof || !dboff || !dgoff || !dG || !db || !dct || !dp || !dm || !dv || !dsv || !dgsv || !dl)
+  short *dfeatT = ds.get<short>((size_t)prows * kClosFeat);
+  ClosGroup *dgroups = ds.get<ClosGroup>(n_groups);
+  double *dG = ds.get<double>(gtot), *dGT = ds.get<double>(gtot), *db = ds.get<double>(rows),
+         *dlp = ds.get<double>(n_groups);
+  ClosState *dnet = ds.get<ClosState>(2);
+  ClosParts *dparts = ds.get<ClosParts>(1);
+  float *dsv = ds.get<float>(prows), *dgsv = ds.get<float>(prows), *da1 = ds.get<float>((size_t)prows * kClosHid),
+        *dl = ds.get<float>(std::max(1, n_steps));
+  if (!dfeat || !dfeatT || !dgroups || !dG || !dGT || !db || !dlp || !dnet || !dparts || !dsv || !dgsv || !da1 || !dl)
     return fail_g(CHFPE_ENOMEM, "closure train scratch");
+  ClosState host;
+  std::copy_n(prm, kClosParams, host.p[0]);
+  std::copy_n(adam_m, kClosParams, host.p[1]);
+  std::copy_n(adam_v, kClosParams, host.p[2]);
   auto up = [&](void *dst, const void *src, size_t bytes) {
     return hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, st) == hipSuccess;
   };
-  if (!up(dgs, group_start, (n_groups + 1) * sizeof(int)) || !up(dgof, gof.data(), rows * sizeof(int)) ||
-      !up(dboff, boff.data(), n_groups * sizeof(int)) || !up(dgoff, goff.data(), n_groups * sizeof(long long)) ||
-      !up(dG, G, gtot * sizeof(double)) || !up(db, b, btot * sizeof(double)) ||
-      !up(dct, ct, 2 * n_groups * sizeof(double)) || !up(dp, prm, kClosParams * sizeof(float)) ||
-      !up(dm, adam_m, kClosParams * sizeof(float)) || !up(dv, adam_v, kClosParams * sizeof(float)))
+  if (!up(dgroups, groups.data(), n_groups * sizeof(ClosGroup)) || !up(dG, G, gtot * sizeof(double)) ||
+      !up(db, b, rows * sizeof(double)) || !up(dnet, &host, sizeof host))
     return fail_g(CHFPE_EDEVICE, "closure train upload");
-  ClosGroups gr{dgs, dgof, dgoff, dboff, dG, db, dct, n_groups};
-  hipLaunchKernelGGL(k_clos_train, dim3(1), dim3(256), 0, st, dp, dm, dv, (int)adam_t0, dfeat, (int)rows, gr,
-                     (int)n_steps, lr, dsv, dgsv, dl);
+  hipLaunchKernelGGL(k_transpose_groups, dim3(n_groups), dim3(256), 0, st, dG, dGT, dgroups);
+  hipLaunchKernelGGL(k_transpose_features, dim3((prows * kClosFeat + 255) / 256), dim3(256), 0, st, dfeat, dfeatT,
+                     (int)rows);
+  for (int step = 0; step <= n_steps; ++step) {
+    const bool last = step == n_steps;  // the last update
+    hipLaunchKernelGGL(k_clos_step, dim3(last ? 1 : n_groups), dim3(64 * kStepWaves), 0, st,
+                       dnet + (step ? (step + 1) % 2 : 0), dnet + step % 2, dparts, (int)adam_t0, step, last ? 1 : 0,
+                       lr, dfeat, (int)rows, dgroups, (int)n_groups, dGT, db, dsv, dgsv, da1, dlp);
+    if (!last)
+      hipLaunchKernelGGL(k_clos_parts, dim3(kPartsBlocks), dim3(64), 0, st, dnet + step % 2, dfeatT, (int)rows, da1,
+                         dgsv, dlp, (int)n_groups, dparts, dl + step);
+  }
   if (hipGetLastError() != hipSuccess) return fail_g(CHFPE_EDEVICE, "closure train launch");
-  bool ok = hipMemcpyAsync(prm, dp, kClosParams * sizeof(float), hipMemcpyDeviceToHost, st) == hipSuccess &&
-            hipMemcpyAsync(adam_m, dm, kClosParams * sizeof(float), hipMemcpyDeviceToHost, st) == hipSuccess &&
-            hipMemcpyAsync(adam_v, dv, kClosParams * sizeof(float), hipMemcpyDeviceToHost, st) == hipSuccess;
+  bool ok = hipMemcpyAsync(&host, dnet + n_steps % 2, sizeof host, hipMemcpyDeviceToHost, st) == hipSuccess;
   if (ok && loss && n_steps > 0)
     ok = hipMemcpyAsync(loss, dl, n_steps * sizeof(float), hipMemcpyDeviceToHost, st) == hipSuccess;
   if (!ok || hipStreamSynchronize(st) != hipSuccess) return fail_g(CHFPE_EDEVICE, "closure train copy");
+  std::copy_n(host.p[0], kClosParams, prm);
+  std::copy_n(host.p[1], kClosParams, adam_m);
+  std::copy_n(host.p[2], kClosParams, adam_v);
   return CHFPE_OK;
 }
 

@@ -465,96 +465,232 @@ k_clos_grad(const float *__restrict__ prm, const short *__restrict__ feat, const
   for (int v = threadIdx.x; v < kClosParams; v += blockDim.x) grad[v] = g[v];
 }
 
-// Training problem: rows grouped by (draw, axis); group q owns rows
-// [gstart[q], gstart[q+1]) and the quadratic (G_q, b_q, c_q, t_q) of its
-// P_q = gstart[q+1] - gstart[q] entries (G_q at goff[q], P_q x P_q; b_q at
-// boff[q]; c_q, t_q at ct[2q], ct[2q + 1]).
-struct ClosGroups {
-  const int *gstart;
-  const int *group_of_row;
-  const long long *goff;
-  const int *boff;
-  const double *G;
-  const double *b;
-  const double *ct;
-  int ngroups;
+// Training problem: rows grouped by (draw, axis); a group owns the P rows of
+// its entries, i0 .. i0 + P - 1, and the quadratic (G, b, c, t): GT[g + f P + e]
+// is G[e][f], b one value per row.
+struct ClosGroup {
+  long long g;
+  int i0, P;
+  double c, t;
 };
 
-// n_steps Adam steps (beta1 0.9, beta2 0.999, eps 1e-8) of the mean group
-// loss, one workgroup of 256 threads.  prm (FP32 master weights) and the
-// moment estimates m, v are read at the start and written back at the end;
-// loss[step] receives the loss at the weights the step starts from.
-// s and gs are scratch arrays of rows floats.
+// GT = every group's P x P matrix transposed (one workgroup per group), so
+// that the rows of a group read consecutive values.
 __global__ void __launch_bounds__(256)
-k_clos_train(float *__restrict__ prm, float *__restrict__ mom1, float *__restrict__ mom2, const int t0,
-             const short *__restrict__ feat, const int rows, const ClosGroups gr, const int n_steps,
-             const float lr, float *__restrict__ s, float *__restrict__ gs, float *__restrict__ loss) {
-  __shared__ ClosNet net;
-  __shared__ ClosBack cb;
-  __shared__ float w[kClosParams], m1[kClosParams], m2[kClosParams], g[kClosParams];
-  __shared__ double lred[256];
-  for (int v = threadIdx.x; v < kClosParams; v += blockDim.x) {
-    w[v] = prm[v];
-    m1[v] = mom1[v];
-    m2[v] = mom2[v];
+k_transpose_groups(const double *__restrict__ G, double *__restrict__ GT, const ClosGroup *__restrict__ groups) {
+  const ClosGroup q = groups[blockIdx.x];
+  for (long long v = threadIdx.x; v < (long long)q.P * q.P; v += blockDim.x) {
+    const long long f = v / q.P, e = v - f * q.P;
+    GT[q.g + v] = G[q.g + e * q.P + f];
   }
+}
+
+// featT[tile][feature][16 rows] = feat, zero past the last row.
+__global__ void __launch_bounds__(256)
+k_transpose_features(const short *__restrict__ feat, short *__restrict__ featT, const int rows) {
+  const int v = blockIdx.x * blockDim.x + threadIdx.x;
+  if (v >= (rows + 15) / 16 * 16 * kClosFeat) return;
+  const int t = v / (16 * kClosFeat), k = v / 16 % kClosFeat, row = 16 * t + v % 16;
+  featT[v] = row < rows ? feat[(long long)row * kClosFeat + k] : (short)0;
+}
+
+// Weights and Adam moments at one step, [w, m, v][kClosParams]; two sets, the
+// steps' in turn.
+struct ClosState {
+  float p[3][kClosParams];
+};
+// Parts of the gradient, summed over c in order: the tiles c, c + 4, ... each.
+constexpr int kTrainChains = 4;
+struct ClosParts {
+  float g[kTrainChains][kClosParams];
+};
+
+// Training takes two launches per step (one workgroup for all steps kept one
+// of 256 CUs busy: 59 thousand tanh of the forward pass for 64 groups of 29
+// entries alone fill its vector units for 17 us).  With one workgroup that
+// recomputed the forward pass in the backward one and gathered each row of G,
+// such a step took 125 us; 14 us now (7 and 5 in the two launches: chains of
+// dependent instructions and of loads another XCD's L2 has just received).
+// Sums keep the order of the four waves that one workgroup had.
+//
+// k_clos_step, one workgroup per group: the Adam step (beta1 0.9, beta2 0.999,
+// eps 1e-8) of the parts that the step before left (every workgroup forms the
+// same weights, the first one stores them), then the network at the group's
+// rows, the loss, and dL/ds of the mean group loss.  gs holds a float and a1
+// 32 floats per row (hidden values, rows of a tile innermost: the layout the
+// backward products read), both padded to whole tiles.  step counts from 0;
+// the launch after the last step updates the weights alone (last).
+constexpr int kStepWaves = 10;
+static_assert(kClosParams <= 64 * kStepWaves, "a parameter per thread");
+__global__ void __launch_bounds__(64 * kStepWaves)
+k_clos_step(const ClosState *__restrict__ from, ClosState *__restrict__ to, const ClosParts *__restrict__ parts,
+            const int t0, const int step, const int last, const float lr, const short *__restrict__ feat,
+            const int rows, const ClosGroup *__restrict__ groups, const int ngroups, const double *__restrict__ GT,
+            const double *__restrict__ b, float *s, float *__restrict__ gs, float *__restrict__ a1,
+            double *__restrict__ lossp) {
+  __shared__ ClosNet net;
+  __shared__ double lred[kStepWaves];
+  const ClosGroup q = groups[blockIdx.x];
+  const int v = threadIdx.x;
+  if (v < kClosParams) {
+    float w = from->p[0][v];
+    if (step > 0) {
+      const float g = ((parts->g[0][v] + parts->g[1][v]) + parts->g[2][v]) + parts->g[3][v];
+      const int tt = t0 + step;
+      const float c1 = 1.f / (1.f - powf(0.9f, (float)tt));
+      const float c2 = 1.f / (1.f - powf(0.999f, (float)tt));
+      const float m1 = fmaf(0.9f, from->p[1][v], 0.1f * g);
+      const float m2 = fmaf(0.001f * g, g, 0.999f * from->p[2][v]);
+      w -= lr * (m1 * c1) / (sqrtf(m2 * c2) + 1e-8f);
+      if (blockIdx.x == 0) {
+        to->p[0][v] = w;
+        to->p[1][v] = m1;
+        to->p[2][v] = m2;
+      }
+    }
+    if (v < kOffB1)
+      net.W1[v] = to_bf16(w);
+    else if (v < kOffW2)
+      net.b1[v - kOffB1] = w;
+    else if (v < kOffB2)
+      net.W2[v - kOffW2] = to_bf16(w);
+    else
+      net.b2 = w;
+  }
+  if (last) return;
   __syncthreads();
   const int wave = threadIdx.x >> 6;
   const int lane = threadIdx.x & 63;
-  const int ntiles = (rows + 15) / 16;
-  const double inv_ng = 1.0 / gr.ngroups;
-  for (int step = 0; step < n_steps; ++step) {
-    clos_load_net(net, w);
-    __syncthreads();
-    // forward
-    for (int t = wave; t < ntiles; t += 4) {
-      float a1[2][4], sv;
-      clos_tile_forward(net, feat, 16 * t, rows, a1, sv);
-      if (lane < 16 && 16 * t + lane < rows) s[16 * t + lane] = sv;
-    }
-    __threadfence_block();
-    __syncthreads();
-    // loss and dL/ds
-    double lp = 0.0;
-    for (int row = threadIdx.x; row < rows; row += blockDim.x) {
-      const int q = gr.group_of_row[row];
-      const int i0 = gr.gstart[q];
-      const int P = gr.gstart[q + 1] - i0;
-      const int e = row - i0;
-      const double *Gq = gr.G + gr.goff[q] + (long long)e * P;
-      double Gs = 0.0;
-      for (int f = 0; f < P; ++f) Gs += Gq[f] * (double)s[i0 + f];
-      const double be = gr.b[gr.boff[q] + e];
-      const double tq = gr.ct[2 * q + 1];
-      const double se = s[row];
-      gs[row] = (float)(2.0 * (Gs - be) / tq * inv_ng);
-      lp += (se * Gs - 2.0 * be * se) / tq * inv_ng;
-      if (e == 0) lp += gr.ct[2 * q] / tq * inv_ng;
-    }
-    lred[threadIdx.x] = lp;
-    __threadfence_block();
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      double a = 0.0;
-      for (int i = 0; i < 256; ++i) a += lred[i];
-      loss[step] = (float)a;
-    }
-    // backward and Adam
-    clos_backward_all(net, feat, rows, gs, cb, g);
-    const int tt = t0 + step + 1;
-    const float c1 = 1.f / (1.f - powf(0.9f, (float)tt));
-    const float c2 = 1.f / (1.f - powf(0.999f, (float)tt));
-    for (int v = threadIdx.x; v < kClosParams; v += blockDim.x) {
-      m1[v] = 0.9f * m1[v] + 0.1f * g[v];
-      m2[v] = 0.999f * m2[v] + 0.001f * g[v] * g[v];
-      w[v] -= lr * (m1[v] * c1) / (sqrtf(m2[v] * c2) + 1e-8f);
-    }
-    __syncthreads();
+  const int kq = 4 * (lane >> 4), rl = lane & 15;
+  // this workgroup's rows, and the padding with the last group's
+  const int i1 = q.i0 + q.P, iend = (int)blockIdx.x == ngroups - 1 ? (rows + 15) / 16 * 16 : i1;
+  for (int t = q.i0 / 16 + wave; 16 * t < iend; t += kStepWaves) {
+    float a[2][4], sv;
+    clos_tile_forward(net, feat, 16 * t, rows, a, sv);
+    const int row = 16 * t + rl;
+    if (row < q.i0 || row >= iend) continue;
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) a1[((long long)t * kClosHid + 16 * hh + kq + j) * 16 + rl] = a[hh][j];
+    if (lane < 16) s[row] = sv;
   }
-  for (int v = threadIdx.x; v < kClosParams; v += blockDim.x) {
-    prm[v] = w[v];
-    mom1[v] = m1[v];
-    mom2[v] = m2[v];
+  __threadfence_block();
+  __syncthreads();
+  double lp = 0.0;
+  const double inv_ng = 1.0 / ngroups;
+  for (int row = q.i0 + threadIdx.x; row < iend; row += blockDim.x) {
+    float gv = 0.f;  // zero past the last row
+    if (row < i1) {
+      const double *Gq = GT + q.g + (row - q.i0);
+      const double be = b[row], se = s[row];
+      double Gs = 0.0;
+#pragma unroll 8
+      for (int f = 0; f < q.P; ++f) Gs += Gq[(long long)f * q.P] * (double)s[q.i0 + f];
+      gv = (float)(2.0 * (Gs - be) / q.t * inv_ng);
+      lp += (se * Gs - 2.0 * be * se) / q.t * inv_ng;
+      if (row == q.i0) lp += q.c / q.t * inv_ng;
+    }
+    gs[row] = gv;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) lp += __shfl_xor(lp, o);
+  if (lane == 0) lred[wave] = lp;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double a = 0.0;
+    for (int i = 0; i < kStepWaves; ++i) a += lred[i];
+    lossp[blockIdx.x] = a;
+  }
+}
+
+// k_clos_parts, one wave per workgroup: the gradient's parts.  Workgroup
+// (role, hidden half hh, chain c) runs over the chain's tiles; a lane holds
+// hidden unit 16 hh + lane % 16 and rows 4 (lane / 16) .. + 3.  role 0: gW1
+// (MFMA); role 1: gW2; role 2: gb1 and gb2; the sums of the last two over rows
+// are first within the lane, then over lane groups.  The last workgroup sums
+// the loss.
+constexpr int kPartsBlocks = 6 * kTrainChains + 1;
+__global__ void __launch_bounds__(64)
+k_clos_parts(const ClosState *__restrict__ st, const short *__restrict__ featT, const int rows,
+             const float *__restrict__ a1, const float *__restrict__ gs, const double *__restrict__ lossp,
+             const int ngroups, ClosParts *__restrict__ parts, float *__restrict__ loss) {
+  const int lane = threadIdx.x;
+  if (blockIdx.x == kPartsBlocks - 1) {
+    double a = 0.0;
+    for (int q = lane; q < ngroups; q += 64) a += lossp[q];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o);
+    if (lane == 0) *loss = (float)a;
+    return;
+  }
+  const int c = blockIdx.x % kTrainChains, hh = blockIdx.x / kTrainChains % 2;
+  const int kq = 4 * (lane >> 4), rl = lane & 15;
+  const int ntiles = (rows + 15) / 16;
+  const float w2 = from_bf16(to_bf16(st->p[0][kOffW2 + 16 * hh + rl]));
+  float *g = parts->g[c];
+  // over the chain's tiles, loads U tiles ahead (tiles past the last: its
+  // values with zero gradients)
+  auto chain = [&](auto &&use) {
+    constexpr int U = 8;
+    f32x4 a[U], gr[U];
+    bf16x4 ph[U];
+    auto load = [&](const int t, const int u) {
+      const int tc = min(t, ntiles - 1);
+      a[u] = *reinterpret_cast<const f32x4 *>(a1 + ((long long)tc * kClosHid + 16 * hh + rl) * 16 + kq);
+      gr[u] = *reinterpret_cast<const f32x4 *>(gs + 16 * tc + kq);
+      ph[u] = *reinterpret_cast<const bf16x4 *>(featT + ((long long)tc * kClosFeat + rl) * 16 + kq);
+    };
+#pragma unroll
+    for (int u = 0; u < U; ++u) load(c + kTrainChains * u, u);
+    for (int t0 = c; t0 < ntiles; t0 += kTrainChains * U) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+        use(a[u], t0 + kTrainChains * u < ntiles ? gr[u] : zero, ph[u]);
+        load(t0 + kTrainChains * (U + u), u);
+      }
+    }
+  };
+  if (blockIdx.x < 2 * kTrainChains) {
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    chain([&](const f32x4 &a, const f32x4 &gsr, const bf16x4 &phiT) {
+      bf16x4 gh;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) gh[j] = to_bf16(gsr[j] * w2 * (1.f - a[j] * a[j]));
+      acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(phiT, gh, acc, 0, 0, 0);
+    });
+#pragma unroll
+    for (int j = 0; j < 4; ++j) g[(kq + j) * kClosHid + 16 * hh + rl] = acc[j];
+    return;
+  }
+  float r[4] = {0.f, 0.f, 0.f, 0.f}, z[4] = {0.f, 0.f, 0.f, 0.f};
+  if (blockIdx.x < 4 * kTrainChains) {
+    chain([&](const f32x4 &a, const f32x4 &gsr, const bf16x4 &) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) r[j] = fmaf(from_bf16(to_bf16(a[j])), from_bf16(to_bf16(gsr[j])), r[j]);
+    });
+  } else {
+    chain([&](const f32x4 &a, const f32x4 &gsr, const bf16x4 &) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        float gh = gsr[j] * w2 * (1.f - a[j] * a[j]);
+        asm volatile("" : "+v"(gh));  // rounded before the sum, as in gW1
+        r[j] += gh;
+        z[j] += gsr[j];
+      }
+    });
+  }
+  // over the sixteen rows: pairs, fours, then the lane groups
+  float v = (r[0] + r[1]) + (r[2] + r[3]), vz = (z[0] + z[1]) + (z[2] + z[3]);
+#pragma unroll
+  for (int o = 16; o < 64; o <<= 1) {
+    v += __shfl_xor(v, o);
+    vz += __shfl_xor(vz, o);
+  }
+  if (kq == 0) {
+    g[(blockIdx.x < 4 * kTrainChains ? kOffW2 : kOffB1) + 16 * hh + rl] = v;
+    if (blockIdx.x >= 4 * kTrainChains && hh == 0 && rl == 0) g[kOffB2] = vz;
   }
 }
 
