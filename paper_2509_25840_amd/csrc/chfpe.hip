@@ -78,6 +78,7 @@ size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 // A dispatch's grid size counts work-items in 32 bits: every launch must stay
 // within it (a larger one would wrap and leave tasks unrun).
 constexpr long long kMaxGridItems = 0xFFFFFFFFLL;
+constexpr int kCUs = 256;            // compute units
 constexpr int kMaxHcChunk = 1024;  // largest k_hcube XCD chunk (tasks)
 
 // work-items of a launch of ntasks workgroups, padded to a multiple of 8
@@ -546,6 +547,19 @@ void plan_two(chfpe_ctx *c, int a, int b, int run, std::vector<int> rest, QPass 
   while (pc > 1 && ((size_t)Na * (Nb + 1) * pc * sizeof(double) > lds_cap || std::max(Na, Nb) * pc > kQThreadsMax))
     pc /= 2;
   out = make_qpass(c, a, b, run, rest, pc);
+  // A launch of a few tasks per CU ends with CUs idle while others do one task
+  // more; tasks of half the width go where they even that out (24^4, one state:
+  // 360 tasks over 256 CUs, 26.5 us a stage launch, 720 tasks 21.5 us).  From 16
+  // points (128 bytes of FP64) down to 8, no further: shorter runs cost more
+  // lines per load than they gain (32^4 at 4 points 93 us against 74).
+  if (c->tune_q_pc <= 0 && pc == 16 && out.pc == pc) {
+    auto even = [&](long long tasks) {  // share of the CUs' time in use, a task each at a time
+      return (double)tasks / (double)((tasks + kCUs - 1) / kCUs * kCUs);
+    };
+    const long long nbat = d.batched ? d.B : 1;
+    const QPass half = make_qpass(c, a, b, run, rest, pc / 2);
+    if (out.ntasks * nbat > kCUs && even(half.ntasks * nbat) > 1.2 * even(out.ntasks * nbat)) out = half;
+  }
   thr = (std::max(Na, Nb) * out.pc + 63) / 64 * 64;
   lds = (size_t)Na * (Nb + 1) * out.pc * sizeof(double);
   nmax = nmax_bucket(std::max(Na, Nb));
