@@ -1742,14 +1742,13 @@ int chfpe_get_state(chfpe_ctx *c, double *host) {
   if (!c->d.hermite)
     hipLaunchKernelGGL((k_sym_scale<double>), dim3(1024), dim3(256), 0, c->stream, c->xb, c->sq, c->sp, c->d.Q,
                        c->d.P, c->d.S, 1);
-  HIPCHK(c, hipMemcpyAsync(host, c->xb, c->d.S * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-  HIPCHK(c, hipStreamSynchronize(c->stream));
+  HIPCHK(c, c->staging.out(host, c->xb, c->d.S * sizeof(double), c->stream));
   return last_launch_error(c);
 }
 
 int chfpe_set_state(chfpe_ctx *c, const double *host) {
   if (!c || !host) return CHFPE_EINVAL;
-  HIPCHK(c, hipMemcpyAsync(c->y, host, c->d.S * sizeof(double), hipMemcpyHostToDevice, c->stream));
+  HIPCHK(c, c->staging.in(c->y, host, c->d.S * sizeof(double), c->stream));
   if (!c->d.hermite)
     hipLaunchKernelGGL((k_sym_scale<double>), dim3(1024), dim3(256), 0, c->stream, c->y, c->sq, c->sp, c->d.Q,
                        c->d.P, c->d.S, 0);

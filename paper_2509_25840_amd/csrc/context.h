@@ -14,6 +14,7 @@
 #include "kernels.h"
 #include "one.h"
 #include "qcube.h"
+#include "staging.h"
 #include "wave.h"
 
 namespace chfpe {
@@ -119,6 +120,7 @@ struct chfpe_ctx {
   std::vector<double> qgrid[3], pgrid[3];
   std::vector<double> wq_host;  // q-point weights (product over q axes), Q entries
   std::vector<double> sq_host;  // exp(-beta U(q)/2), Q entries
+  Staging staging;  // host copies of whole states
   double *rbuf = nullptr;
   size_t rbuf_cap = 0;
   std::string err = "no error";
