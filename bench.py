@@ -251,15 +251,21 @@ def _kind_of(short: str, grid: int, min_grid: dict):
     targs = [a.strip() for a in short[short.find("<") + 1:short.rfind(">")].split(",")] if "<" in short else []
     if fam == "k_pblock":
         kind = "perturb" if targs[5] == "true" else "pblock_rhs"  # <T, TO, NMAX, RPT, MM, PERTURB, CLOS>
-    elif fam in ("k_pcube", "k_pcube_s", "k_pwave"):
-        kind = "perturb" if targs[4] == "true" else "pcube_rhs"  # <T, TO, NB1, SPLIT or NVR, PERTURB[, CLOS]>
+    elif fam in ("k_pcube", "k_pwave"):
+        kind = "perturb" if targs[4] == "true" else "pcube_rhs"  # <T, TO, NB1, SPLIT or NVR, PERTURB, CLOS>
+    elif fam == "k_pcube_s":
+        kind = "perturb" if targs[3] == "true" else "pcube_rhs"  # <T, TO, NB1, PERTURB>
+    elif fam == "k_pwave2":
+        kind = "perturb" if targs[4] == "true" else "pblock_rhs"  # <T, TO, NB, NVR, PERTURB, CLOS>
     elif fam == "k_qpass":
         if int(targs[5]) == 2:        # dX/dq field: second launch of a perturbation
             kind = "perturb_q"
         else:
             kind = _EPI_KIND[int(targs[4])]
     elif fam == "k_hcube":
-        kind = _HEPI_KIND[int(targs[3])]  # <T, NB1, SPLIT, EPI>
+        kind = _HEPI_KIND[int(targs[2])]  # <T, NB1, EPI>
+    elif fam == "k_qcube":
+        kind = "qpass_rk4"  # <T, NB>: the stage update is an argument, one kind for all
     elif fam == "k_hwave":
         kind = "hcube_rk4"  # <T, NB, NVR, MM>: the stage update is an argument, one kind for all
     elif fam == "k_hperturb":

@@ -299,8 +299,8 @@ int chfpe_kernel_times(chfpe_ctx *ctx, int32_t max_kinds, int64_t *counts, doubl
                        double *mean_bytes, const char **names);
 
 /* Tile autotuner.  Times one RK4 step (after one untimed step), averaged
- * over n_steps (1..1000), for each candidate tile shape: first the k_pblock
- * shapes (blocks per task 1, 2, 4, 8 where the block fits, with and
+ * over n_steps (1..1000), for each candidate tile shape: first the shape in
+ * use, then the k_pblock shapes (blocks per task 1, 2, 4, 8 where the block fits, with and
  * without lane-pair line solves), then the q-pass tile widths 4, 8, 16, 32
  * (positions of the contiguous run per two-axis tile, as LDS allows) with
  * the best k_pblock shape, then the k_pblock task order (runs of 1, 4, 8,
@@ -327,9 +327,12 @@ int chfpe_autotune(chfpe_ctx *ctx, int32_t n_steps);
  * variables reproduce; out[9] the k_pblock task order (consecutive block
  * groups of one state before the next element) and out[10] its request
  * (0 = 1; CHFPE_TUNE_PB_RUN); out[11] 1 when one workgroup per q point takes
- * the whole p block (k_pcube; out[0], out[9] then describe no launch), out[12]
- * 1 when that kernel is the streamed form k_pcube_s (the default for p_1
- * axes up to 16 points; CHFPE_TUNE_PC_STREAM=0/1 forces either form).
+ * the whole p block (out[0], out[9] then describe no launch), out[12] 1 when
+ * that kernel is a streamed form: k_pwave (three modes, p axes up to 24 points)
+ * or k_pcube_s (the default for p_1 axes up to 16 points otherwise), 0 for
+ * k_pcube; CHFPE_TUNE_PC_STREAM=0/1 forces either.  Two modes with p axes up to
+ * 32 points run k_pwave2 unless a k_pblock or k_pcube shape is asked for
+ * (CHFPE_PWAVE2=0 does so too); out[0..2] and out[9] then describe no launch.
  * Hermite basis: out[13] the k_hcube tasks per XCD chunk (the XCDs take
  * chunks of consecutive tasks in turn; 0: one contiguous range each) and
  * out[14] the width of the k_2 tiles of its task order (three modes; 1

@@ -10,8 +10,10 @@
 // right-hand side).  One RK4 step is the degree-4 Taylor polynomial of the
 // generator, which classical RK4 equals for a linear time-independent
 // system, in nested form (four stages, see Epi in kernels.h).  A stage is one
-// p-axis launch (k_pblock, or k_pcube for three modes) followed by one or two
-// k_qpass launches, the last of which applies the stage update.
+// p-axis launch (k_pwave2 for two modes, k_pwave for three, k_pblock or k_pcube
+// where those do not fit) followed by k_qcube, or by one or two k_qpass launches,
+// the last of which applies the stage update.  One mode runs whole propagations
+// in k_one; a Hermite stage is one launch of k_hwave or k_hcube.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -571,9 +573,10 @@ void plan_one(chfpe_ctx *c, int a, int run, std::vector<int> rest, QPass &out, i
   nmax = nmax_bucket(axis_len(c->d, a));
 }
 
-// Three modes take k_pcube wherever its block fits (CHFPE_PCUBE=0 keeps the
-// p-block path where that one tiles); two modes take it only for p blocks
-// the p-block tile cannot cover (p axes above 32 points).
+// Three modes take all p axes of a q point in one task (k_pwave or k_pcube)
+// wherever the block fits (CHFPE_PCUBE=0 keeps the p-block path where that one
+// tiles); two modes take k_pcube only for p blocks the p-block tile cannot
+// cover (p axes above 32 points).
 bool use_pcube(const chfpe_ctx *c) {
   const Derived &d = c->d;
   if (!pcube_shape_ok(d)) return false;
@@ -621,7 +624,6 @@ bool plan(chfpe_ctx *c) {
     h.nblk = hcube_nblk(h.ntasks, h.chunk);
     ln.hcube_nb1 = nmax_bucket(h.N1);
     ln.hcube_threads = (h.plane + 63) / 64 * 64;
-    ln.hcube_split = h.N1 == ln.hcube_nb1 && h.N2 == h.N1 && h.N3 == h.N1;
     // the wave-plane form, where the launch over every state fits one dispatch;
     // two modes take the q grid as one (q_1, q_2) plane
     ln.hwave = false;
@@ -698,18 +700,18 @@ bool plan(chfpe_ctx *c) {
     pq.nblk = pad8(pq.ntasks);
     ln.pcube_nb1 = nmax_bucket(pq.N1);
     ln.pcube_threads = (pq.plane + 63) / 64 * 64;
-    // row pad of the LDS planes (CHFPE_TUNE_PC_PAD, 1..8), kept only while the LDS fits
-    // the streamed form where its workgroups gain occupancy (p_1 up to 16
-    // points: four-wave workgroups); CHFPE_TUNE_PC_STREAM=0/1 forces either
+    // k_pwave for p axes up to 24 points (its figures), else the streamed
+    // k_pcube_s where its workgroups gain occupancy (p_1 up to 16 points:
+    // four-wave workgroups); CHFPE_TUNE_PC_STREAM=0/1 forces either
     ln.pwave_nb = nmax_bucket(std::max(pq.N1, std::max(pq.N2, pq.N3)));
     ln.pwave = M == 3 && ln.pwave_nb <= 24 && c->tune_pc_stream != 0 &&
                grid_items((long long)pq.ntasks * nbat, 64 * pwave_nw(pq, ln.pwave_nb)) <= kMaxGridItems;
     ln.pcube_stream = ln.pwave || (c->tune_pc_stream >= 0 ? (c->tune_pc_stream > 0 && nmax_bucket(d.Np[0]) <= 32)
                                                           : nmax_bucket(d.Np[0]) <= 16);
+    // row pad of the LDS planes (CHFPE_TUNE_PC_PAD, 1..8), kept only while the LDS fits
     pq.rs = pq.N3 + 1;
     if (!ln.pcube_stream && c->tune_pc_pad > 1 && pcube_lds_bytes(d, sizeof(double), c->tune_pc_pad, false) <= 160 * 1024)
       pq.rs = pq.N3 + c->tune_pc_pad;
-    ln.pcube_lds = pcube_lds_bytes(d, sizeof(double), pq.rs - pq.N3, ln.pcube_stream);
     ln.pcube_split = pq.N1 == ln.pcube_nb1 && pq.N2 == pq.N1 && pq.N3 == pq.N1 && c->tune_pb_split != 0;
     pb.nb = 1;  // k_pblock is not launched: one shape for the autotuner
     pb.split = ln.pcube_split ? 1 : 0;
@@ -742,8 +744,9 @@ bool plan(chfpe_ctx *c) {
     ln.has_qx = true;
     plan_one(c, M + 0, plane, {0, 1, 2}, ln.qx, ln.qx_threads, ln.qx_nmax);
   }
-  // two modes: k_pwave2 where a wave's lines hold the p axes and no k_pblock or
-  // k_pcube form is asked for by name
+  // two modes: k_pwave2 where half a wave holds an axis' lines (up to 32 points;
+  // 27 x 28 points 44 us against k_pblock's 72, 16^2 9 against 11) and no k_pblock
+  // or k_pcube form is asked for by name
   ln.pwave2 = false;
   if (M == 2 && std::max(d.Np[0], d.Np[1]) <= 32 && c->allow_pwave2 && c->tune_pb_nb <= 0 && c->tune_pb_split < 0 &&
       c->tune_pb_run <= 0 && c->tune_pc_stream < 0) {

@@ -73,13 +73,12 @@ struct Launch {
   // three modes: every q derivative and the stage update in one pass (k_qcube)
   bool qcube = false;
   // Hermite basis: k_hcube over the q cube of each (branch, element, k)
-  bool hcube = false, hcube_split = false;
+  bool hcube = false;
   PCube hcb{};
   int hcube_threads = 0, hcube_nb1 = 0;
   bool hwave = false;  // k_hwave (three modes, q axes of at most 24 points; two modes, 32)
   int hwave_nb = 0;
   int pcube_threads = 0, pcube_nb1 = 0;
-  size_t pcube_lds = 0;
   // one mode: whole propagations by one workgroup per state (k_one)
   bool one = false;
   int qa_threads = 0, qf_threads = 0, qx_threads = 0;

@@ -23,11 +23,15 @@
 //                Liouvillian, Phi and the derivative part of Theta.  For
 //                three modes the p_1 derivative of G_{n,1} is taken by a
 //                k_qpass over (q_1, p_1), which forms that field itself.
+//   k_pcube, k_pwave, k_pwave2 -- the same with every p axis of a q point in one
+//                task (wave.h holds the wave-plane forms, the usual ones).
 //   k_qpass   -- the -(p_s/m_s) D_{q_s} W_n terms.  A tile is one or two
 //                q axes at full length times a chunk of consecutive p-block
 //                positions; each thread holds one q_a line in registers, a
 //                second q_b axis goes through LDS.  The last q pass of a
 //                stage also applies the classical RK4 stage update.
+//   k_qcube (qcube.h) -- all q axes and the stage update in one pass, for small
+//                cubes; k_one (one.h): whole propagations of one mode.
 //
 // All state arithmetic is in the template type T (double, or float for FP32
 // branch states); tables and reductions are FP64.
@@ -1031,9 +1035,8 @@ k_pcube(const Geom g, const Tabs tb, const PCube pc, const T *__restrict__ X, TO
 // complete, takes its forward Thomas step.  Every value is read once (no copy
 // of the block), so the LDS holds only a round's two planes and the first ND
 // forward results d_j of every line (the rest stay in registers); the back
-// substitution then writes t.  At 24^3 in FP64 that is 78 KB of LDS and
-// 96 VGPRs: two workgroups per CU, where k_pcube's block copy allows one.
-// Plain stencils only (a closure keeps k_pcube).
+// substitution then writes t.  Plain stencils only (a closure keeps k_pcube).
+// It is left to what k_pwave does not take: a p axis above 24 points.
 
 // Task constants of k_pcube_s in LDS: slots of the groups below (three
 // modes each) and the damping, then the p_2 and p_3 grids.
@@ -1042,15 +1045,9 @@ constexpr int kCfP2 = 20, kCfP3 = kCfP2 + kTab;
 constexpr int kPCubeCF = kCfP3 + kTab;
 constexpr int pcube_s_planes(const int nb1) { return nb1 >= 24 ? 2 : nb1 / 4; }
 constexpr int pcube_s_dlds(const int tsize, const int nb1) { return tsize == 8 && nb1 >= 24 ? nb1 / 2 + 1 : 0; }
-// Waves per SIMD the register budget aims at: five for the cubic FP64 24^3
-// block (two workgroups of nine waves per CU).
-template <typename T, int NB1, bool SPLIT>
-constexpr int pcube_s_waves() {
-  return sizeof(T) == 8 && NB1 == 24 && SPLIT ? 5 : 4;
-}
 
-template <typename T, typename TO, int NB1, bool SPLIT, bool PERTURB>
-__global__ void __launch_bounds__((pcube_max_threads<T, NB1>()), (pcube_s_waves<T, NB1, SPLIT>()))
+template <typename T, typename TO, int NB1, bool PERTURB>
+__global__ void __launch_bounds__((pcube_max_threads<T, NB1>()), 4)
 k_pcube_s(const Geom g, const Tabs tb, const PCube pc, const T *__restrict__ X, TO *__restrict__ out,
           const double *__restrict__ grad) {
   constexpr int PL = pcube_s_planes(NB1);          // planes per round
@@ -1061,10 +1058,8 @@ k_pcube_s(const Geom g, const Tabs tb, const PCube pc, const T *__restrict__ X, 
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int task = xcd_task(blockIdx.x, pc.nblk);
   if (task >= pc.ntasks) return;
-  // SPLIT blocks are cubes of NB1 points: their loops have fixed trip counts
-  const int N1 = SPLIT ? NB1 : pc.N1, N2 = SPLIT ? NB1 : pc.N2, N3 = SPLIT ? NB1 : pc.N3;
-  const int plane = SPLIT ? NB1 * NB1 : pc.plane;
-  const int rs = SPLIT ? NB1 + 1 : pc.rs;  // LDS row stride (p_3 row plus a pad)
+  const int N1 = pc.N1, N2 = pc.N2, N3 = pc.N3, plane = pc.plane;
+  const int rs = pc.rs;                     // LDS row stride (p_3 row plus a pad)
   T *CF = reinterpret_cast<T *>(smem_raw);  // task constants, kPCubeCF values
   T *G2 = CF + kPCubeCF;                    // [PL][N2][rs]
   T *G3 = G2 + PL * N2 * rs;
@@ -1201,26 +1196,13 @@ k_pcube_s(const Geom g, const Tabs tb, const PCube pc, const T *__restrict__ X, 
     // p_2 lines of G2 (fixed k, j3) and p_3 lines of G3 (fixed k, j2)
     const int npl = min(PL, N1 - i0);
     const int nl2 = npl * N3, nl = nl2 + npl * N2;
-    if (SPLIT) {
 #pragma unroll 1
-      for (int hl = tid; hl < 2 * nl; hl += blockDim.x) {
-        const int l = hl >> 1;
-        if (l < nl2) {
-          const int k = l / N3, c = l - k * N3;
-          compact_split<T, NB1>(G2, k * N2 * rs + c, rs, hl & 1, T(g.dp_ca[1]), T(g.dp_cb[1]));
-        } else {
-          compact_split<T, NB1>(G3, (l - nl2) * rs, 1, hl & 1, T(g.dp_ca[2]), T(g.dp_cb[2]));
-        }
-      }
-    } else {
-#pragma unroll 1
-      for (int l = tid; l < nl; l += blockDim.x) {
-        if (l < nl2) {
-          const int k = l / N3, c = l - k * N3;
-          compact_lds<T>(G2, k * N2 * rs + c, rs, N2, T(g.dp_ca[1]), T(g.dp_cb[1]));
-        } else {
-          compact_lds<T>(G3, (l - nl2) * rs, 1, N3, T(g.dp_ca[2]), T(g.dp_cb[2]));
-        }
+    for (int l = tid; l < nl; l += blockDim.x) {
+      if (l < nl2) {
+        const int k = l / N3, c = l - k * N3;
+        compact_lds<T>(G2, k * N2 * rs + c, rs, N2, T(g.dp_ca[1]), T(g.dp_cb[1]));
+      } else {
+        compact_lds<T>(G3, (l - nl2) * rs, 1, N3, T(g.dp_ca[2]), T(g.dp_cb[2]));
       }
     }
     __syncthreads();
@@ -1547,7 +1529,7 @@ __device__ __forceinline__ int hcube_kl(const Geom &g, const int T, const int kb
   return (k1 * N2 + k2) * N3 + k3;
 }
 
-template <typename T, int NB1, bool SPLIT, int EPI>
+template <typename T, int NB1, int EPI>
 __global__ void __launch_bounds__((hcube_max_threads<T, NB1>()))
 k_hcube(const Geom g, const Tabs tb, const PCube pc, const T *__restrict__ X, const T *__restrict__ y,
         T *__restrict__ out, const double cst) {
@@ -1558,9 +1540,7 @@ k_hcube(const Geom g, const Tabs tb, const PCube pc, const T *__restrict__ X, co
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int task = pc.chunk > 0 ? xcd_chunk_task(blockIdx.x, pc.chunk) : xcd_task(blockIdx.x, pc.nblk);
   if (task >= pc.ntasks) return;
-  const int N1 = SPLIT ? NB1 : pc.N1, N2 = SPLIT ? NB1 : pc.N2, N3 = SPLIT ? NB1 : pc.N3;
-  const int plane = SPLIT ? NB1 * NB1 : pc.plane;
-  const int rs = SPLIT ? NB1 + 1 : pc.rs;
+  const int N1 = pc.N1, N2 = pc.N2, N3 = pc.N3, plane = pc.plane, rs = pc.rs;
   T *CF = reinterpret_cast<T *>(smem_raw);
   T *G2 = CF + kHCubeCF;  // [PL][N2][rs]
   T *G3 = G2 + PL * N2 * rs;
@@ -1673,26 +1653,13 @@ k_hcube(const Geom g, const Tabs tb, const PCube pc, const T *__restrict__ X, co
     // q_2 lines of G2 (fixed k, j3) and q_3 lines of G3 (fixed k, j2)
     const int npl = min(PL, N1 - i0);
     const int nl2 = npl * N3, nl = nl2 + npl * N2;
-    if (SPLIT) {
 #pragma unroll 1
-      for (int hl = tid; hl < 2 * nl; hl += blockDim.x) {
-        const int l = hl >> 1;
-        if (l < nl2) {
-          const int k = l / N3, c = l - k * N3;
-          compact_split<T, NB1>(G2, k * N2 * rs + c, rs, hl & 1, T(g.dq_ca[1]), T(g.dq_cb[1]));
-        } else {
-          compact_split<T, NB1>(G3, (l - nl2) * rs, 1, hl & 1, T(g.dq_ca[2]), T(g.dq_cb[2]));
-        }
-      }
-    } else {
-#pragma unroll 1
-      for (int l = tid; l < nl; l += blockDim.x) {
-        if (l < nl2) {
-          const int k = l / N3, c = l - k * N3;
-          compact_lds<T>(G2, k * N2 * rs + c, rs, N2, T(g.dq_ca[1]), T(g.dq_cb[1]));
-        } else {
-          compact_lds<T>(G3, (l - nl2) * rs, 1, N3, T(g.dq_ca[2]), T(g.dq_cb[2]));
-        }
+    for (int l = tid; l < nl; l += blockDim.x) {
+      if (l < nl2) {
+        const int k = l / N3, c = l - k * N3;
+        compact_lds<T>(G2, k * N2 * rs + c, rs, N2, T(g.dq_ca[1]), T(g.dq_cb[1]));
+      } else {
+        compact_lds<T>(G3, (l - nl2) * rs, 1, N3, T(g.dq_ca[2]), T(g.dq_cb[2]));
       }
     }
     __syncthreads();

@@ -5,24 +5,13 @@ namespace chfpe {
 
 // Hermite basis: one k_hcube launch computes the right-hand side of X and
 // the stage update (EPI, coefficient cst) over every (branch, element, k).
-template <typename T, int NB1, bool SPLIT, int EPI>
-void launch_hcube_k(chfpe_ctx *c, const Batch &b, const T *X, const T *y, T *xo, double cst) {
+template <typename T, int NB1, int EPI>
+void launch_hcube_n(chfpe_ctx *c, const Batch &b, const T *X, const T *y, T *xo, double cst) {
   const size_t lds = (kHCubeCF + 2 * (size_t)kHCubePL * b.hcb.N2 * b.hcb.rs) * sizeof(T);
-  auto kern = k_hcube<T, NB1, SPLIT, EPI>;
+  auto kern = k_hcube<T, NB1, EPI>;
   allow_lds(kern, lds);
   hipLaunchKernelGGL(kern, dim3(b.hcb.nblk), dim3(c->ln.hcube_threads), lds, c->stream, b.g, c->tb, b.hcb, X, y,
                      xo, cst);
-}
-
-template <typename T, int NB1, int EPI>
-void launch_hcube_n(chfpe_ctx *c, const Batch &b, const T *X, const T *y, T *xo, double cst) {
-  if constexpr (NB1 <= 24) {  // cubes of 32 or 48 points exceed the workgroup: never lane pairs
-    if (c->ln.hcube_split) {
-      launch_hcube_k<T, NB1, true, EPI>(c, b, X, y, xo, cst);
-      return;
-    }
-  }
-  launch_hcube_k<T, NB1, false, EPI>(c, b, X, y, xo, cst);
 }
 
 template <typename T, int EPI>
