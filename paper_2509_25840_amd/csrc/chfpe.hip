@@ -549,18 +549,28 @@ void plan_two(chfpe_ctx *c, int a, int b, int run, std::vector<int> rest, QPass 
   while (pc > 1 && ((size_t)Na * (Nb + 1) * pc * sizeof(double) > lds_cap || std::max(Na, Nb) * pc > kQThreadsMax))
     pc /= 2;
   out = make_qpass(c, a, b, run, rest, pc);
-  // A launch of a few tasks per CU ends with CUs idle while others do one task
-  // more; tasks of half the width go where they even that out (24^4, one state:
-  // 360 tasks over 256 CUs, 26.5 us a stage launch, 720 tasks 21.5 us).  From 16
-  // points (128 bytes of FP64) down to 8, no further: shorter runs cost more
-  // lines per load than they gain (32^4 at 4 points 93 us against 74).
+  // Half the width, 8 points (64 bytes of FP64), in two cases; no further, as
+  // shorter runs cost more lines per load than they gain (32^4 at 4 points 93 us
+  // a stage launch against 74).
   if (c->tune_q_pc <= 0 && pc == 16 && out.pc == pc) {
+    // (1) A launch of a few tasks per CU ends with CUs idle while others do one
+    // task more; narrower tasks where they even that out (24^4, one state: 360
+    // tasks over 256 CUs, 26.5 us a stage launch, 720 tasks 21.5 us).
     auto even = [&](long long tasks) {  // share of the CUs' time in use, a task each at a time
       return (double)tasks / (double)((tasks + kCUs - 1) / kCUs * kCUs);
     };
     const long long nbat = d.batched ? d.B : 1;
     const QPass half = make_qpass(c, a, b, run, rest, pc / 2);
-    if (out.ntasks * nbat > kCUs && even(half.ntasks * nbat) > 1.2 * even(out.ntasks * nbat)) out = half;
+    const bool uneven = out.ntasks * nbat > kCUs && even(half.ntasks * nbat) > 1.2 * even(out.ntasks * nbat);
+    // (2) q lines of 17 to 32 points that do not fill their registers (measured;
+    // the cause was not isolated): (q_2, q_3) passes of 18 x 17 q points 0.92 ->
+    // 0.61 ms, 22 x 20 1.01 -> 0.77, 20^2 FP32 1.28 -> 1.14, 26 x 30 0.251 ->
+    // 0.236; two modes of 18 x 22, 16 states, 0.230 -> 0.184, 28 x 30 0.595 ->
+    // 0.583.  Shorter ones lose (13 x 15 0.121 -> 0.135), and full ones: 32^2 4.03
+    // -> 4.34, 24^2 FP32 2.4 -> 2.8; 24^2 FP64 gains 0 to 10%, left with FP32.
+    const int fill = nmax_bucket(std::max(Na, Nb));
+    const bool part = b < d.M && (fill == 24 || fill == 32) && (Na != fill || Nb != fill);
+    if (uneven || part) out = half;
   }
   thr = (std::max(Na, Nb) * out.pc + 63) / 64 * 64;
   lds = (size_t)Na * (Nb + 1) * out.pc * sizeof(double);
