@@ -349,7 +349,7 @@ def summarise_counters(args, kern_cmd: str) -> None:
         passes.append(names)
         for r in rows:
             s = _short_name(r["Kernel_Name"])
-            if not s.startswith(("k_pcube", "k_pwave", "k_qpass", "k_pblock", "k_hcube", "k_hwave")):
+            if not s.startswith(("k_pcube", "k_pwave", "k_qpass", "k_qcube", "k_pblock", "k_hcube", "k_hwave")):
                 continue
             key = (s, _grid(r))
             per.setdefault(key, {})

@@ -1967,7 +1967,8 @@ int chfpe_autotune(chfpe_ctx *c, int32_t n_steps) {
     c->tune_q_pc = t.q_pc;
     c->tune_pb_run = t.pb_run;
     if (!plan(c)) return CHFPE_OK;  // too large a launch for one dispatch: not a candidate
-    const std::vector<int> eff = {c->ln.pb.nb, c->ln.pb.split, c->ln.qf.pc, c->ln.qa.pc, c->ln.pb.run,
+    const int split = c->ln.pwave ? 0 : c->ln.pb.split;  // (k_pwave has one line solve)
+    const std::vector<int> eff = {c->ln.pb.nb, split, c->ln.qf.pc, c->ln.qa.pc, c->ln.pb.run,
                                   c->ln.pwave2};
     for (const auto &s : seen)
       if (s == eff) return CHFPE_OK;  // same launches as a shape already timed
