@@ -385,9 +385,8 @@ int chfpe_closure_grad(const float *prm, const float *feat, int32_t rows, const 
                        void *hip_stream);
 
 /* n_steps Adam steps (beta1 0.9, beta2 0.999, eps 1e-8, step lr) of the mean
- * over groups of (s^T G s - 2 b^T s + c) / t, all on the device in one
- * workgroup.  Group q owns rows [group_start[q], group_start[q+1]) (covering
- * 0..rows) with G (P_q x P_q, groups concatenated), b, and (c, t) in ct.
+ * over groups of (s^T G s - 2 b^T s + c) / t, all on the device.  Group q
+ * owns rows [group_start[q], group_start[q+1]) (covering 0..rows) with G (P_q x P_q, groups concatenated), b, and (c, t) in ct.
  * prm, adam_m, adam_v (577 each) are read and written back; adam_t0 is the
  * number of steps already taken; loss (n_steps, may be NULL) receives the
  * loss at the parameters each step starts from. */
