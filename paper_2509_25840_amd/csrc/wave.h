@@ -684,8 +684,10 @@ k_pwave2(const Geom g, const Tabs tb, const PCube pc, const T *__restrict__ X, T
 // A missing neighbour is the task's own block with zero factors (an L1 hit).
 // Per stage, before and after: 24^3 x 12^3 FP64 4.9 -> 2.5 ms, four FP32
 // states 12.4 -> 6.9 ms; 32^2 x 16^2 FP64 0.140 -> 0.024 ms.  At 24^3 it is
-// bound by the reads that miss L2 (6.7 states a launch, 7 TB/s with the
-// writes; its twelve neighbour blocks and the force tables).
+// bound by the reads that miss L2 (FP64: 8.1 states a launch, 6.9 TB/s with the
+// writes; its twelve neighbour blocks and the force tables).  The task order
+// set for k_hcube is its best too: chunks of 10 to 240 tasks and k_2 tiles of 2
+// to 6 move it by -0.5 to +6%, one range per XCD by +18%.
 constexpr int hwave_npw(const int nb, const bool exact, const int mm) { return mm == 2 ? 1 : pwave_npw(nb, exact); }
 constexpr int hwave_ps(const int nb, const bool exact, const int mm) { return mm == 2 ? 1 : wave_ps(nb, exact); }
 constexpr int hwave_waves(const int nb, const bool exact, const int mm) {
