@@ -770,15 +770,6 @@ k_hwave(const Geom g, const Tabs tb, const PCube pc, const T *__restrict__ X, co
   const T dmp = uniform(T(tb.damp[e]));
   const int tl = min(tid, NB - 1);
   const T tv1 = MM == 3 ? T(tb.Vp[tl]) : T(0), tv2 = T(tb.Vp[A2 * kTab + tl]), tv3 = T(tb.Vp[A3 * kTab + tl]);
-  auto fill_tables = [&]() {
-    if (tid < NB) {
-      V1[tid] = tv1;
-      V2[tid] = tv2;
-      V3[tid] = tv3;
-    }
-    __syncthreads();
-  };
-
   // vectors of this lane (as in k_pwave)
   constexpr int PER0 = NB / V / wave_gcd(NB / V, 64);
   constexpr int DR = 64 * V * PER0 / NB;
@@ -814,25 +805,24 @@ k_hwave(const Geom g, const Tabs tb, const PCube pc, const T *__restrict__ X, co
     Vec<T, V> c, u[MM], d[MM], a[MM], b[MM];
     Vec<double, V> F[MM];
   };
+  auto load = [&](auto UP, const int k, const int m) {
+    In x;
+    const uint32_t at = point(k, m);
+    x.c = get(Xe, at);
+#pragma unroll
+    for (int s = 0; s < MM; ++s) {
+      x.u[s] = get(Xu[s], at);
+      x.d[s] = get(Xd[s], at);
+      if constexpr (decltype(UP)::value) x.a[s] = get(Hu[s], at);
+      x.b[s] = get(Hd[s], at);
+      x.F[s] = get(tb.F + s * Q, at);
+    }
+    return x;
+  };
   T sv[NPW][NV][V];
   auto sweep = [&](auto UP) {
     constexpr bool up = decltype(UP)::value;
-    auto load = [&](const int k, const int m) {
-      In x;
-      const uint32_t at = point(k, m);
-      x.c = get(Xe, at);
-#pragma unroll
-      for (int s = 0; s < MM; ++s) {
-        x.u[s] = get(Xu[s], at);
-        x.d[s] = get(Xd[s], at);
-        if constexpr (up) x.a[s] = get(Hu[s], at);
-        x.b[s] = get(Hd[s], at);
-        x.F[s] = get(tb.F + s * Q, at);
-      }
-      return x;
-    };
-    In nxt = load(0, 0);
-    fill_tables();
+    In nxt = load(UP, 0, 0);
 #pragma unroll
     for (int k = 0; k < NPW; ++k) {
       const int i0 = MM == 2 ? 0 : (w + k * nw) * PS;
@@ -868,9 +858,9 @@ k_hwave(const Geom g, const Tabs tb, const PCube pc, const T *__restrict__ X, co
           sv[k][m][q] = s;
         }
         if (m + 1 < NV)
-          nxt = load(k, m + 1);
+          nxt = load(UP, k, m + 1);
         else if (k + 1 < NPW && (EXACT || i0 + nw * PS < N1))
-          nxt = load(k + 1, 0);
+          nxt = load(UP, k + 1, 0);
         if (mine(m)) {
 #pragma unroll
           for (int q = 0; q < V; ++q) GA[at_a(m) + q] = f2.v[q];
@@ -898,7 +888,16 @@ k_hwave(const Geom g, const Tabs tb, const PCube pc, const T *__restrict__ X, co
       }
     }
   };
-  if (any_up)  // uniform: the elements below the hierarchy's last level
+  // The V' tables come to LDS before the waves part: two modes give each wave a
+  // task of its own, so the branch below is uniform over a wave alone and holds
+  // no barrier.
+  if (tid < NB) {
+    V1[tid] = tv1;
+    V2[tid] = tv2;
+    V3[tid] = tv3;
+  }
+  __syncthreads();
+  if (any_up)  // the elements below the hierarchy's last level
     sweep(std::true_type{});
   else
     sweep(std::false_type{});

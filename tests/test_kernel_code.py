@@ -1,0 +1,39 @@
+"""Properties of the compiled kernels that no run can show: instantiations are
+compiled to gfx950 assembly here (no GPU is needed) and their instructions read.
+"""
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_2509_25840_amd import build as hip_build
+
+ARGS = {"k_hwave": "const Geom, const Tabs, const PCube, const {T} *, const {T} *, {T} *, const double, const int",
+        "k_pwave": "const Geom, const Tabs, const PCube, const {T} *, {T} *, const double *",
+        "k_pwave2": "const Geom, const Tabs, const PCube, const {T} *, {T} *, const double *"}
+
+
+def assembly(tmp_path, kernel, T, args):
+    """The assembly of one instantiation, a list of instruction lines."""
+    if not os.path.exists(hip_build.HIPCC):
+        pytest.skip("no hipcc")
+    src, out = tmp_path / "one.hip", tmp_path / "one.s"
+    src.write_text('#include "wave.h"\nnamespace chfpe {\n'
+                   f"template __global__ void {kernel}<{args}>({ARGS[kernel].format(T=T)});\n}}\n")
+    subprocess.run([hip_build.HIPCC, *hip_build.FLAGS, "-I", os.path.join(hip_build.ROOT, "include"), "-I",
+                    hip_build.CSRC, "--cuda-device-only", "-S", str(src), "-o", str(out)], check=True,
+                   stderr=subprocess.DEVNULL)
+    return [ln.strip() for ln in out.read_text().splitlines() if re.match(r"\s+[a-z]", ln)]
+
+
+@pytest.mark.parametrize("args,barriers", [("double, 8, 0, 2", 1), ("double, 24, 6, 2", 1), ("float, 16, 0, 2", 1),
+                                           ("double, 8, 0, 3", 3), ("float, 12, 3, 3", 3)])
+def test_no_barrier_of_k_hwave_is_under_a_branch(tmp_path, args, barriers):
+    """The waves of a two-mode workgroup hold tasks of different hierarchy
+    elements and branch on them, so the one barrier (the tables are in LDS)
+    comes before that branch; with a copy in either path the waves of a
+    workgroup would wait at different barriers.  Three modes have two more,
+    around the q_1 lines."""
+    code = assembly(tmp_path, "k_hwave", args.split(",")[0], args)
+    assert sum(ln.startswith("s_barrier") for ln in code) == barriers
