@@ -697,7 +697,7 @@ constexpr size_t hwave_lds_vals(const int nb, const int n1, const int n2, const 
                                 const int mm) {
   return (mm == 2 ? 2 * (size_t)nw * (wave_slot(n2, n3, 1) + 16)
                   : (size_t)(n1 + nw * ps) * wave_slot(n2, n3, ps) + wave_pad(nb, ps)) +
-         3 * (size_t)nb;
+         (mm == 2 ? 2 * (size_t)nw : 3) * (size_t)nb;
 }
 constexpr int hwave_occ(const int nb, const int tsize) { return nb >= 24 ? 2 : tsize == 4 ? 4 : 3; }
 
@@ -727,7 +727,9 @@ k_hwave(const Geom g, const Tabs tb, const PCube pc, const T *__restrict__ X, co
   const int slot = wave_slot(N2, N3, PS);
   T *tiles = reinterpret_cast<T *>(smem_raw);
   T *own = tiles + (MM == 2 ? nw * (slot + 16) : N1 * slot + wave_pad(NB, PS));
-  T *V1 = own + (MM == 2 ? nw * (slot + 16) : nw * PS * slot), *V2 = V1 + NB, *V3 = V2 + NB;
+  // V' by mode; two modes: a copy per wave (V1 stays unused)
+  T *V1 = own + (MM == 2 ? nw * (slot + 16) : nw * PS * slot);
+  T *V2 = MM == 2 ? V1 + 2 * w * NB : V1 + NB, *V3 = V2 + NB;
   const int per_br = g.ne * g.P;
   const int br = task / per_br;
   const int kb = (task - br * per_br) / g.ne;
@@ -768,8 +770,24 @@ k_hwave(const Geom g, const Tabs tb, const PCube pc, const T *__restrict__ X, co
     }
   }
   const T dmp = uniform(T(tb.damp[e]));
-  const int tl = min(tid, NB - 1);
+  // The V' tables come to LDS behind the first loads of the planes.  Three modes:
+  // the workgroup has one task, one element, and meets at a barrier.  Two modes:
+  // the waves branch apart on their elements below, so each keeps its own copy
+  // and waits for nobody.
+  const int ti = MM == 2 ? lane : tid, tl = min(ti, NB - 1);
   const T tv1 = MM == 3 ? T(tb.Vp[tl]) : T(0), tv2 = T(tb.Vp[A2 * kTab + tl]), tv3 = T(tb.Vp[A3 * kTab + tl]);
+  auto fill_tables = [&]() {
+    if (ti < NB) {
+      if constexpr (MM == 3) V1[ti] = tv1;
+      V2[ti] = tv2;
+      V3[ti] = tv3;
+    }
+    if constexpr (MM == 3)
+      __syncthreads();
+    else
+      wave_lds_fence();
+  };
+
   // vectors of this lane (as in k_pwave)
   constexpr int PER0 = NB / V / wave_gcd(NB / V, 64);
   constexpr int DR = 64 * V * PER0 / NB;
@@ -805,24 +823,25 @@ k_hwave(const Geom g, const Tabs tb, const PCube pc, const T *__restrict__ X, co
     Vec<T, V> c, u[MM], d[MM], a[MM], b[MM];
     Vec<double, V> F[MM];
   };
-  auto load = [&](auto UP, const int k, const int m) {
-    In x;
-    const uint32_t at = point(k, m);
-    x.c = get(Xe, at);
-#pragma unroll
-    for (int s = 0; s < MM; ++s) {
-      x.u[s] = get(Xu[s], at);
-      x.d[s] = get(Xd[s], at);
-      if constexpr (decltype(UP)::value) x.a[s] = get(Hu[s], at);
-      x.b[s] = get(Hd[s], at);
-      x.F[s] = get(tb.F + s * Q, at);
-    }
-    return x;
-  };
   T sv[NPW][NV][V];
   auto sweep = [&](auto UP) {
     constexpr bool up = decltype(UP)::value;
-    In nxt = load(UP, 0, 0);
+    auto load = [&](const int k, const int m) {
+      In x;
+      const uint32_t at = point(k, m);
+      x.c = get(Xe, at);
+#pragma unroll
+      for (int s = 0; s < MM; ++s) {
+        x.u[s] = get(Xu[s], at);
+        x.d[s] = get(Xd[s], at);
+        if constexpr (up) x.a[s] = get(Hu[s], at);
+        x.b[s] = get(Hd[s], at);
+        x.F[s] = get(tb.F + s * Q, at);
+      }
+      return x;
+    };
+    In nxt = load(0, 0);
+    fill_tables();
 #pragma unroll
     for (int k = 0; k < NPW; ++k) {
       const int i0 = MM == 2 ? 0 : (w + k * nw) * PS;
@@ -858,9 +877,9 @@ k_hwave(const Geom g, const Tabs tb, const PCube pc, const T *__restrict__ X, co
           sv[k][m][q] = s;
         }
         if (m + 1 < NV)
-          nxt = load(UP, k, m + 1);
+          nxt = load(k, m + 1);
         else if (k + 1 < NPW && (EXACT || i0 + nw * PS < N1))
-          nxt = load(UP, k + 1, 0);
+          nxt = load(k + 1, 0);
         if (mine(m)) {
 #pragma unroll
           for (int q = 0; q < V; ++q) GA[at_a(m) + q] = f2.v[q];
@@ -888,16 +907,7 @@ k_hwave(const Geom g, const Tabs tb, const PCube pc, const T *__restrict__ X, co
       }
     }
   };
-  // The V' tables come to LDS before the waves part: two modes give each wave a
-  // task of its own, so the branch below is uniform over a wave alone and holds
-  // no barrier.
-  if (tid < NB) {
-    V1[tid] = tv1;
-    V2[tid] = tv2;
-    V3[tid] = tv3;
-  }
-  __syncthreads();
-  if (any_up)  // the elements below the hierarchy's last level
+  if (any_up)  // the elements below the hierarchy's last level; uniform over a task
     sweep(std::true_type{});
   else
     sweep(std::false_type{});
