@@ -44,15 +44,16 @@ template <typename T, int V>
 struct alignas(sizeof(T) * V) Vec {
   T v[V];
 };
-// values at byte offset voff (per lane) + soff (uniform)
+// values at byte offset voff; the instruction's uniform offset stays zero, as
+// the intrinsic leaves it out of the comparison with the buffer's size
 template <typename T, int V>
-__device__ __forceinline__ Vec<T, V> buf_load(const Buf r, const uint32_t voff, const uint32_t soff) {
+__device__ __forceinline__ Vec<T, V> buf_load(const Buf r, const uint32_t voff) {
   if constexpr (sizeof(T) * V == 16)
-    return __builtin_bit_cast(Vec<T, V>, __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, 0));
+    return __builtin_bit_cast(Vec<T, V>, __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, 0, 0));
   else if constexpr (sizeof(T) * V == 8)
-    return __builtin_bit_cast(Vec<T, V>, __builtin_amdgcn_raw_buffer_load_b64(r, (int)voff, (int)soff, 0));
+    return __builtin_bit_cast(Vec<T, V>, __builtin_amdgcn_raw_buffer_load_b64(r, (int)voff, 0, 0));
   else
-    return __builtin_bit_cast(Vec<T, V>, __builtin_amdgcn_raw_buffer_load_b32(r, (int)voff, (int)soff, 0));
+    return __builtin_bit_cast(Vec<T, V>, __builtin_amdgcn_raw_buffer_load_b32(r, (int)voff, 0, 0));
 }
 // Closure weights of one axis in LDS: rows p1, m1, p2, m2 of NB entries (third
 // off-diagonals are not used, kClosBands = 2).
@@ -382,18 +383,19 @@ k_pwave(const Geom g, const Tabs tb, const PCube pc, const T *__restrict__ X, TO
     constexpr bool up = decltype(UP)::value;
     // The plane offset passes through an empty asm statement each time: the
     // buffers are read-only, and without it every load of the kernel may be
-    // hoisted to the top.
+    // hoisted to the top.  It is part of the offset per lane, the one that is
+    // compared with the buffer's size.
     auto load = [&](const int k, const int m) {
       In x;
       uint32_t so = (uint32_t)((w + k * nw) * (PS * plane)) * (uint32_t)sizeof(T);
       asm volatile("" : "+s"(so));
-      const uint32_t vo = (uint32_t)(lane + 64 * m) * (uint32_t)(V * sizeof(T));
-      x.h = buf_load<T, V>(bh, vo, so);
+      const uint32_t vo = so + (uint32_t)(lane + 64 * m) * (uint32_t)(V * sizeof(T));
+      x.h = buf_load<T, V>(bh, vo);
       if constexpr (!PERTURB) {
 #pragma unroll
         for (int s = 0; s < 3; ++s) {
-          if constexpr (up) x.u[s] = buf_load<T, V>(bu[s], vo, so);
-          x.d[s] = buf_load<T, V>(bd[s], vo, so);
+          if constexpr (up) x.u[s] = buf_load<T, V>(bu[s], vo);
+          x.d[s] = buf_load<T, V>(bd[s], vo);
         }
       }
       return x;
@@ -600,12 +602,12 @@ k_pwave2(const Geom g, const Tabs tb, const PCube pc, const T *__restrict__ X, T
     In x;
     uint32_t vo = (uint32_t)(lane + 64 * m) * (uint32_t)(V * sizeof(T));
     asm volatile("" : "+v"(vo));  // keeps the loads where they are issued (see k_pwave)
-    x.h = buf_load<T, V>(bh, vo, 0);
+    x.h = buf_load<T, V>(bh, vo);
     if constexpr (!PERTURB) {
 #pragma unroll
       for (int s = 0; s < 2; ++s) {
-        x.u[s] = buf_load<T, V>(bu[s], vo, 0);
-        x.d[s] = buf_load<T, V>(bd[s], vo, 0);
+        x.u[s] = buf_load<T, V>(bu[s], vo);
+        x.d[s] = buf_load<T, V>(bd[s], vo);
       }
     }
     return x;

@@ -34,3 +34,18 @@ def test_the_waves_of_two_mode_k_hwave_meet_at_no_barrier(tmp_path, args):
     workgroup would wait at different ones."""
     code = assembly(tmp_path, "k_hwave", args.split(",")[0], args)
     assert not any(ln.startswith("s_barrier") for ln in code)
+
+
+@pytest.mark.parametrize("kernel,args", [("k_pwave", "double, double, 8, 1, false, false"),
+                                         ("k_pwave", "double, double, 24, 0, false, false"),
+                                         ("k_pwave", "double, double, 24, 9, false, false"),
+                                         ("k_pwave", "float, float, 16, 0, false, false"),
+                                         ("k_pwave2", "double, double, 16, 4, false, false")])
+def test_buffer_loads_keep_their_whole_offset_under_the_bounds_check(tmp_path, kernel, args):
+    """Loads past a block, and of a neighbour that is not there, rely on the
+    buffer's size.  Only the offset per lane is compared with it, so the
+    instruction's scalar offset (the operand before "offen") has to be zero."""
+    code = [ln for ln in assembly(tmp_path, kernel, args.split(",")[0], args) if ln.startswith("buffer_load")]
+    assert code
+    for ln in code:
+        assert re.search(r", 0 offen( offset:\d+)?$", ln), ln
