@@ -341,6 +341,18 @@ int chfpe_autotune(chfpe_ctx *ctx, int32_t n_steps);
  * Writes min(n, 15) values and returns that count. */
 int chfpe_tile_config(const chfpe_ctx *ctx, int32_t *out, int32_t n);
 
+/* Kernels that a context of these parameters runs, under the present CHFPE_*
+ * environment (host only, no device call): out[0] the p side of right-hand
+ * sides and excitations of one FP64 state (1 k_pblock, 2 k_pcube, 3 k_pcube_s,
+ * 4 k_pwave, 5 k_pwave2; Hermite basis: the whole stage, 6 k_hcube, 7 k_hwave),
+ * out[1] the same for the branch states of a batched context (0 otherwise),
+ * out[2] for an FP64 state with a closure (0 where chfpe_set_closure refuses),
+ * out[3] the q side (1 k_qpass, 2 k_qcube; 0 Hermite basis), out[4] the q side
+ * with a closure (0 as out[2]), out[5] 1 where one-mode propagations run whole
+ * in k_one.  Writes min(n, 6) values and returns that count; EINVAL where
+ * chfpe_setup refuses the parameters. */
+int chfpe_kernel_plan(const chfpe_params *p, int32_t *out, int32_t n);
+
 /* ---- Learned per-axis closure (coarse grids) -------------------------------
  * The paper discretises every axis with the compact scheme of Sec. III B on
  * one grid.  A closure lets a coarse grid (half the points per axis of a fine

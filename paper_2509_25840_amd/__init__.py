@@ -121,6 +121,8 @@ def lib():
     L.chfpe_autotune.restype = ctypes.c_int
     L.chfpe_tile_config.argtypes = [vp, ctypes.POINTER(i32), i32]
     L.chfpe_tile_config.restype = ctypes.c_int
+    L.chfpe_kernel_plan.argtypes = [P, ctypes.POINTER(i32), i32]
+    L.chfpe_kernel_plan.restype = ctypes.c_int
     fp = ctypes.POINTER(ctypes.c_float)
     ip = ctypes.POINTER(i32)
     L.chfpe_closure_rows.argtypes = [P]
@@ -185,6 +187,20 @@ def optical_from_dict(X: dict) -> Optical:
 
 def workspace_bytes(p: Params) -> int:
     return int(lib().chfpe_workspace_bytes(ctypes.byref(p)))
+
+
+KERNELS = ("", "k_pblock", "k_pcube", "k_pcube_s", "k_pwave", "k_pwave2", "k_hcube", "k_hwave")
+
+
+def kernel_plan(p: Params) -> dict:
+    """chfpe_kernel_plan as a dict of kernel names ("" where nothing runs)."""
+    out = (ctypes.c_int32 * 6)()
+    k = lib().chfpe_kernel_plan(ctypes.byref(p), out, 6)
+    if k < 0:
+        raise ChfpeError(k, lib().chfpe_last_error(None).decode())
+    q = ("", "k_qpass", "k_qcube")
+    return {"state": KERNELS[out[0]], "branches": KERNELS[out[1]], "closure": KERNELS[out[2]], "q": q[out[3]],
+            "q_closure": q[out[4]], "one": bool(out[5])}
 
 
 def stream_copy(dst, src, nbytes: int, stream=None) -> None:

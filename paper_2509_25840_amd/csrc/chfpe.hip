@@ -23,6 +23,7 @@
 #include <cstring>
 #include <functional>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -609,6 +610,36 @@ bool use_qcube(const chfpe_ctx *c, long long nbat) {
          grid_items((long long)d.ne * ((d.P + run - 1) / run) * nbat, n * n * kQcParts) <= kMaxGridItems;
 }
 
+// Requested tile shapes and kernels: what the autotuner kept for this shape,
+// then the environment.
+void read_requests(chfpe_ctx *c) {
+  {
+    std::lock_guard<std::mutex> lk(g_tune_mu);
+    auto it = g_tuned.find(tune_key(c->d));
+    if (it != g_tuned.end()) {
+      c->tune_pb_nb = it->second.pb_nb;
+      c->tune_pb_split = it->second.pb_split;
+      c->tune_q_pc = it->second.q_pc;
+      c->tune_pb_run = it->second.pb_run;
+    }
+  }
+  if (const char *v = std::getenv("CHFPE_TUNE_PB_NB")) c->tune_pb_nb = std::atoi(v);
+  if (const char *v = std::getenv("CHFPE_TUNE_Q_PC")) c->tune_q_pc = std::atoi(v);
+  if (const char *v = std::getenv("CHFPE_TUNE_PB_SPLIT")) c->tune_pb_split = std::atoi(v);
+  if (const char *v = std::getenv("CHFPE_TUNE_PB_RUN")) c->tune_pb_run = std::atoi(v);
+  if (const char *v = std::getenv("CHFPE_TUNE_PC_PAD")) c->tune_pc_pad = std::max(0, std::min(8, std::atoi(v)));
+  if (const char *v = std::getenv("CHFPE_TUNE_PC_STREAM")) c->tune_pc_stream = std::atoi(v);
+  if (const char *v = std::getenv("CHFPE_TUNE_HC_CHUNK")) c->tune_hc_chunk = std::atoi(v);
+  if (const char *v = std::getenv("CHFPE_TUNE_HC_KTILE")) c->tune_hc_ktile = std::atoi(v);
+  if (const char *v = std::getenv("CHFPE_NO_GRAPH")) c->use_graphs = std::atoi(v) == 0;
+  if (const char *v = std::getenv("CHFPE_PCUBE")) c->allow_pcube = std::atoi(v) != 0;
+  if (const char *v = std::getenv("CHFPE_PWAVE")) c->allow_pwave = std::atoi(v) != 0;
+  if (const char *v = std::getenv("CHFPE_HWAVE")) c->allow_hwave = std::atoi(v) != 0;
+  if (const char *v = std::getenv("CHFPE_PWAVE2")) c->allow_pwave2 = std::atoi(v) != 0;
+  if (const char *v = std::getenv("CHFPE_QCUBE")) c->allow_qcube = std::atoi(v) != 0;
+  if (const char *v = std::getenv("CHFPE_ONE")) c->allow_one = std::atoi(v) != 0;
+}
+
 // Choose tile shapes.  Returns false when a k_qpass launch over every state
 // of the largest batch would exceed one dispatch (the k_pblock shape always
 // fits: derive() checked it).
@@ -638,7 +669,7 @@ bool plan(chfpe_ctx *c) {
     // two modes take the q grid as one (q_1, q_2) plane
     ln.hwave = false;
     ln.hwave_nb = nmax_bucket(*std::max_element(d.Nq, d.Nq + M));
-    if (M >= 2 && ln.hwave_nb <= (M == 3 ? 24 : 32)) {
+    if (M >= 2 && c->allow_hwave && ln.hwave_nb <= (M == 3 ? 24 : 32)) {
       PCube hw = h;
       if (M == 2) {
         hw.N1 = 1;
@@ -714,7 +745,7 @@ bool plan(chfpe_ctx *c) {
     // k_pcube_s where its workgroups gain occupancy (p_1 up to 16 points:
     // four-wave workgroups); CHFPE_TUNE_PC_STREAM=0/1 forces either
     ln.pwave_nb = nmax_bucket(std::max(pq.N1, std::max(pq.N2, pq.N3)));
-    ln.pwave = M == 3 && ln.pwave_nb <= 24 && c->tune_pc_stream != 0 &&
+    ln.pwave = M == 3 && ln.pwave_nb <= 24 && c->allow_pwave && c->tune_pc_stream != 0 &&
                grid_items((long long)pq.ntasks * nbat, 64 * pwave_nw(pq, ln.pwave_nb)) <= kMaxGridItems;
     ln.pcube_stream = ln.pwave || (c->tune_pc_stream >= 0 ? (c->tune_pc_stream > 0 && nmax_bucket(d.Np[0]) <= 32)
                                                           : nmax_bucket(d.Np[0]) <= 16);
@@ -775,6 +806,29 @@ bool plan(chfpe_ctx *c) {
   return fits(ln.qf, ln.qf_threads) && (!ln.has_qa || fits(ln.qa, ln.qa_threads)) &&
          (!ln.has_qx || fits(ln.qx, ln.qx_threads)) &&
          (!ln.pcube || grid_items((long long)ln.pcb.ntasks * nbat, ln.pcube_threads) <= kMaxGridItems);
+}
+
+// The requested shapes, or where those are too small for this batch, automatic ones.
+bool plan_any(chfpe_ctx *c) {
+  if (plan(c)) return true;
+  c->tune_pb_nb = 0;
+  c->tune_pb_split = -1;
+  c->tune_q_pc = 0;
+  c->tune_pb_run = 0;
+  return plan(c);
+}
+
+// Kernel of the p side of a right-hand side or excitation, or of a whole
+// Hermite stage, over states of tsize-byte values, with a closure or without
+// (the numbers are those of chfpe_kernel_plan).
+enum PKernel : int { PK_PBLOCK = 1, PK_PCUBE, PK_PCUBE_S, PK_PWAVE, PK_PWAVE2, PK_HCUBE, PK_HWAVE };
+PKernel p_kernel(const chfpe_ctx *c, size_t, bool clos) {
+  const Launch &ln = c->ln;
+  if (ln.hcube) return ln.hwave ? PK_HWAVE : PK_HCUBE;
+  if (ln.pwave2) return PK_PWAVE2;
+  if (!ln.pcube) return PK_PBLOCK;
+  if (ln.pwave) return PK_PWAVE;
+  return ln.pcube_stream && !clos ? PK_PCUBE_S : PK_PCUBE;
 }
 
 // --------------------------------------------------------------------------
@@ -864,34 +918,37 @@ Batch batch_of(const chfpe_ctx *c, int nb) {
   return b;
 }
 
+// p side of a right-hand side, or of an excitation (PERTURB), by kernel pk
+template <typename T, typename TO, bool PERTURB>
+void launch_p(chfpe_ctx *c, const Batch &b, PKernel pk, const T *X, TO *out, const double *grad) {
+  switch (pk) {
+    case PK_PWAVE2: launch_pwave2<T, TO, PERTURB>(c, b, X, out, grad); break;
+    case PK_PWAVE: launch_pwave<T, TO, PERTURB>(c, b, X, out, grad); break;
+    case PK_PBLOCK: launch_pblock_t<T, TO, PERTURB>(c, b, X, out, grad); break;
+    default: launch_pcube_t<T, TO, PERTURB>(c, b, X, out, grad); break;
+  }
+}
+
 // One right-hand-side evaluation of X (t: partial right-hand side) fused with
 // the stage epilogue EPI (coefficient cst); all buffers hold b.g.nbatch
 // states.  kind: the timing kind of the stage-final launch.
 template <typename T, int EPI>
 void launch_stage(chfpe_ctx *c, const Batch &b, const T *X, T *t, const T *y, T *xo, double cst, int kind) {
   const Launch &ln = c->ln;
+  const PKernel pk = p_kernel(c, sizeof(T), c->closure_on);
   if (ln.hcube) {  // Hermite basis: the whole stage in one launch
     const int hk = EPI == EPI_H1 ? K_HS1 : EPI == EPI_H4 ? K_HS4 : EPI == EPI_OUT ? K_HOUT
                    : kind == K_QS3 ? K_HS3 : K_HS2;
     TimedScope ts(c, hk, b.g.nbatch, sizeof(T));
-    if (ln.hwave)
+    if (pk == PK_HWAVE)
       launch_hwave<T>(c, b, X, y, xo, cst, EPI);
     else
       launch_hcube<T, EPI>(c, b, X, y, xo, cst);
     return;
   }
-  if (ln.pwave2) {
+  {
     TimedScope ts(c, ln.pcube ? K_PCUBE : K_PBLOCK, b.g.nbatch, sizeof(T));
-    launch_pwave2<T, T, false>(c, b, X, t, nullptr);
-  } else if (ln.pcube) {
-    TimedScope ts(c, K_PCUBE, b.g.nbatch, sizeof(T));
-    if (ln.pwave)
-      launch_pwave<T, T, false>(c, b, X, t, nullptr);
-    else
-      launch_pcube_t<T, T, false>(c, b, X, t, nullptr);
-  } else {
-    TimedScope ts(c, K_PBLOCK, b.g.nbatch, sizeof(T));
-    launch_pblock_t<T, T, false>(c, b, X, t, nullptr);
+    launch_p<T, T, false>(c, b, pk, X, t, nullptr);
   }
   if (ln.qcube && !c->closure_on) {
     TimedScope ts(c, kind, b.g.nbatch, sizeof(T));
@@ -924,18 +981,7 @@ void launch_perturb(chfpe_ctx *c, const double *W, TO *out, const double *grad) 
     hipLaunchKernelGGL((k_hperturb<TO>), dim3(2048), dim3(256), 0, c->stream, b.g, W, out, grad);
     return;
   }
-  if (c->ln.pwave2) {
-    launch_pwave2<double, TO, true>(c, b, W, out, grad);
-    return;
-  }
-  if (c->ln.pcube) {
-    if (c->ln.pwave)
-      launch_pwave<double, TO, true>(c, b, W, out, grad);
-    else
-      launch_pcube_t<double, TO, true>(c, b, W, out, grad);
-    return;
-  }
-  launch_pblock_t<double, TO, true>(c, b, W, out, grad);
+  launch_p<double, TO, true>(c, b, p_kernel(c, sizeof(double), c->closure_on), W, out, grad);
   if (c->ln.has_qx)
     launch_q_t<double, TO, false, EPI_ACC, FX, FQ>(c, b, b.qx, c->ln.qx_threads, 0, c->ln.qx_nmax, W, out,
                                                    nullptr, nullptr, grad, 0.0);
@@ -1447,29 +1493,7 @@ int chfpe_setup(const chfpe_params *p, void *dev_workspace, size_t ws_bytes, voi
     for (int i = 0; i < kBranchBufs; ++i) c->bb[i] = at(L.bbufs[i]);
 
   make_geom(c);
-  {
-    std::lock_guard<std::mutex> lk(g_tune_mu);
-    auto it = g_tuned.find(tune_key(d));
-    if (it != g_tuned.end()) {
-      c->tune_pb_nb = it->second.pb_nb;
-      c->tune_pb_split = it->second.pb_split;
-      c->tune_q_pc = it->second.q_pc;
-      c->tune_pb_run = it->second.pb_run;
-    }
-  }
-  if (const char *v = std::getenv("CHFPE_TUNE_PB_NB")) c->tune_pb_nb = std::atoi(v);
-  if (const char *v = std::getenv("CHFPE_TUNE_Q_PC")) c->tune_q_pc = std::atoi(v);
-  if (const char *v = std::getenv("CHFPE_TUNE_PB_SPLIT")) c->tune_pb_split = std::atoi(v);
-  if (const char *v = std::getenv("CHFPE_TUNE_PB_RUN")) c->tune_pb_run = std::atoi(v);
-  if (const char *v = std::getenv("CHFPE_TUNE_PC_PAD")) c->tune_pc_pad = std::max(0, std::min(8, std::atoi(v)));
-  if (const char *v = std::getenv("CHFPE_TUNE_PC_STREAM")) c->tune_pc_stream = std::atoi(v);
-  if (const char *v = std::getenv("CHFPE_TUNE_HC_CHUNK")) c->tune_hc_chunk = std::atoi(v);
-  if (const char *v = std::getenv("CHFPE_TUNE_HC_KTILE")) c->tune_hc_ktile = std::atoi(v);
-  if (const char *v = std::getenv("CHFPE_NO_GRAPH")) c->use_graphs = std::atoi(v) == 0;
-  if (const char *v = std::getenv("CHFPE_PCUBE")) c->allow_pcube = std::atoi(v) != 0;
-  if (const char *v = std::getenv("CHFPE_PWAVE2")) c->allow_pwave2 = std::atoi(v) != 0;
-  if (const char *v = std::getenv("CHFPE_QCUBE")) c->allow_qcube = std::atoi(v) != 0;
-  if (const char *v = std::getenv("CHFPE_ONE")) c->allow_one = std::atoi(v) != 0;
+  read_requests(c);
   std::vector<double> F, Vp, pm, pg, sq, sp, wp, cc, tc, damp;
   std::vector<int> up, dn;
   build_tables(c, F, Vp, pm, pg, sq, sp, wp, up, dn, cc, tc, damp);
@@ -1490,16 +1514,10 @@ int chfpe_setup(const chfpe_params *p, void *dev_workspace, size_t ws_bytes, voi
       return fail(nullptr, CHFPE_EINVAL, "box too large: exp(-beta H/2) underflows at its edge");
     }
   }
-  if (!plan(c)) {  // requested q tiles too small for this batch: automatic ones
-    c->tune_pb_nb = 0;
-    c->tune_pb_split = -1;
-    c->tune_q_pc = 0;
-    c->tune_pb_run = 0;
-    if (!plan(c)) {
-      chfpe_destroy(c);
-      return fail(nullptr, CHFPE_EINVAL,
-                  "batch too large: a q-pass launch over every branch state exceeds one dispatch (2^32 work-items)");
-    }
+  if (!plan_any(c)) {
+    chfpe_destroy(c);
+    return fail(nullptr, CHFPE_EINVAL,
+                "batch too large: a q-pass launch over every branch state exceeds one dispatch (2^32 work-items)");
   }
 
   auto up_copy = [&](void *dst, const void *src, size_t bytes) {
@@ -1538,6 +1556,31 @@ int chfpe_setup(const chfpe_params *p, void *dev_workspace, size_t ws_bytes, voi
   c->tb.clos = reinterpret_cast<const double *>(at(L.clos));
   *out = c;
   return CHFPE_OK;
+}
+
+int chfpe_kernel_plan(const chfpe_params *p, int32_t *out, int32_t n) {
+  if (!out || n < 0) return fail(nullptr, CHFPE_EINVAL, "invalid arguments");
+  const std::unique_ptr<chfpe_ctx> c(new chfpe_ctx());  // (no device call)
+  std::string err;
+  if (!derive(p, c->d, err)) return fail(nullptr, CHFPE_EINVAL, err);
+  const Derived &d = c->d;
+  c->prm = *p;
+  make_geom(c.get());
+  read_requests(c.get());
+  if (!plan_any(c.get())) return fail(nullptr, CHFPE_EINVAL, "batch too large for one dispatch");
+  bool clos = !d.hermite && d.prec == CHFPE_FP64;
+  for (int s = 0; s < d.M; ++s) clos = clos && d.Nq[s] <= 16 && d.Np[s] <= 16;
+  const Launch &ln = c->ln;
+  const size_t bsize = d.prec == CHFPE_FP32 ? sizeof(float) : sizeof(double);
+  const int32_t v[6] = {p_kernel(c.get(), sizeof(double), false),
+                        d.batched ? p_kernel(c.get(), bsize, false) : 0,
+                        clos ? p_kernel(c.get(), sizeof(double), true) : 0,
+                        d.hermite ? 0 : ln.qcube ? 2 : 1,
+                        clos ? 1 : 0,
+                        ln.one ? 1 : 0};
+  const int k = std::min<int>(n, 6);
+  for (int i = 0; i < k; ++i) out[i] = v[i];
+  return k;
 }
 
 int chfpe_equilibrate(chfpe_ctx *c, int64_t n_steps, double dt) {

@@ -135,6 +135,8 @@ struct chfpe_ctx {
   bool closure_on = false; // right-hand sides use the closure stencil weights (tb.clos)
   bool use_graphs = true;
   bool allow_pcube = true;  // three modes: k_pcube where the p block fits it
+  bool allow_pwave = true;  // three modes: k_pwave where a wave's lines hold the p axes
+  bool allow_hwave = true;  // Hermite basis: k_hwave where a wave's lines hold the q axes
   bool allow_pwave2 = true; // two modes: k_pwave2 where a wave's lines hold the p axes
   bool allow_qcube = true;  // three modes: k_qcube where the q cube fits it
   bool allow_one = true;    // one mode: k_one where the state fits it
