@@ -328,11 +328,14 @@ int chfpe_autotune(chfpe_ctx *ctx, int32_t n_steps);
  * groups of one state before the next element) and out[10] its request
  * (0 = 1; CHFPE_TUNE_PB_RUN); out[11] 1 when one workgroup per q point takes
  * the whole p block (out[0], out[9] then describe no launch), out[12] 1 when
- * that kernel is a streamed form: k_pwave (three modes, p axes up to 24 points)
- * or k_pcube_s (the default for p_1 axes up to 16 points otherwise), 0 for
- * k_pcube; CHFPE_TUNE_PC_STREAM=0/1 forces either.  Two modes with p axes up to
- * 32 points run k_pwave2 unless a k_pblock or k_pcube shape is asked for
- * (CHFPE_PWAVE2=0 does so too); out[0..2] and out[9] then describe no launch.
+ * that block fits a streamed form: k_pwave (three modes, p axes up to 24
+ * points, where its planes are large enough to pay) or k_pcube_s (the default
+ * for p_1 axes up to 16 points otherwise), 0 where k_pcube alone takes it;
+ * CHFPE_TUNE_PC_STREAM=0/1 forces k_pcube or a streamed form.  Two modes with
+ * p axes up to 32 points run k_pwave2, but for small planes of many states,
+ * unless a k_pblock or k_pcube shape is asked for (CHFPE_PWAVE2=0 does so too);
+ * out[0..2] and out[9] then describe no launch.  Where k_qcube runs, out[3..5]
+ * describe none but a closure's.  chfpe_kernel_plan names the kernels.
  * Hermite basis: out[13] the k_hcube tasks per XCD chunk (the XCDs take
  * chunks of consecutive tasks in turn; 0: one contiguous range each) and
  * out[14] the width of the k_2 tiles of its task order (three modes; 1

@@ -741,17 +741,18 @@ bool plan(chfpe_ctx *c) {
     pq.nblk = pad8(pq.ntasks);
     ln.pcube_nb1 = nmax_bucket(pq.N1);
     ln.pcube_threads = (pq.plane + 63) / 64 * 64;
-    // k_pwave for p axes up to 24 points (its figures), else the streamed
-    // k_pcube_s where its workgroups gain occupancy (p_1 up to 16 points:
-    // four-wave workgroups); CHFPE_TUNE_PC_STREAM=0/1 forces either
+    // k_pwave for p axes up to 24 points where it pays (see p_kernel), else the
+    // streamed k_pcube_s where its workgroups gain occupancy (p_1 up to 16
+    // points: four-wave workgroups); CHFPE_TUNE_PC_STREAM=0/1 forces k_pcube or a
+    // streamed form
     ln.pwave_nb = nmax_bucket(std::max(pq.N1, std::max(pq.N2, pq.N3)));
     ln.pwave = M == 3 && ln.pwave_nb <= 24 && c->allow_pwave && c->tune_pc_stream != 0 &&
                grid_items((long long)pq.ntasks * nbat, 64 * pwave_nw(pq, ln.pwave_nb)) <= kMaxGridItems;
-    ln.pcube_stream = ln.pwave || (c->tune_pc_stream >= 0 ? (c->tune_pc_stream > 0 && nmax_bucket(d.Np[0]) <= 32)
-                                                          : nmax_bucket(d.Np[0]) <= 16);
+    ln.pcube_s = c->tune_pc_stream >= 0 ? (c->tune_pc_stream > 0 && nmax_bucket(d.Np[0]) <= 32)
+                                        : nmax_bucket(d.Np[0]) <= 16;
     // row pad of the LDS planes (CHFPE_TUNE_PC_PAD, 1..8), kept only while the LDS fits
     pq.rs = pq.N3 + 1;
-    if (!ln.pcube_stream && c->tune_pc_pad > 1 && pcube_lds_bytes(d, sizeof(double), c->tune_pc_pad, false) <= 160 * 1024)
+    if (!ln.pcube_s && c->tune_pc_pad > 1 && pcube_lds_bytes(d, sizeof(double), c->tune_pc_pad, false) <= 160 * 1024)
       pq.rs = pq.N3 + c->tune_pc_pad;
     ln.pcube_split = pq.N1 == ln.pcube_nb1 && pq.N2 == pq.N1 && pq.N3 == pq.N1 && c->tune_pb_split != 0;
     pb.nb = 1;  // k_pblock is not launched: one shape for the autotuner
@@ -819,16 +820,21 @@ bool plan_any(chfpe_ctx *c) {
 }
 
 // Kernel of the p side of a right-hand side or excitation, or of a whole
-// Hermite stage, over states of tsize-byte values, with a closure or without
+// Hermite stage, over nb states of tsize-byte values, with a closure or without
 // (the numbers are those of chfpe_kernel_plan).
 enum PKernel : int { PK_PBLOCK = 1, PK_PCUBE, PK_PCUBE_S, PK_PWAVE, PK_PWAVE2, PK_HCUBE, PK_HWAVE };
-PKernel p_kernel(const chfpe_ctx *c, size_t, bool clos) {
+PKernel p_kernel(const chfpe_ctx *c, int nb, size_t tsize, bool clos) {
   const Launch &ln = c->ln;
-  if (ln.hcube) return ln.hwave ? PK_HWAVE : PK_HCUBE;
-  if (ln.pwave2) return PK_PWAVE2;
+  if (ln.hcube) {
+    const bool pays = c->d.M == 2 || hwave_pays(ln.hwave_nb, ln.hcb.N1, ln.hcb.plane, tsize);
+    return ln.hwave && pays ? PK_HWAVE : PK_HCUBE;
+  }
+  // (k_pcube is two modes' other form only where k_pblock does not tile)
+  if (ln.pwave2 && (ln.pcube || clos || pwave2_pays(ln.pwave2_nb, ln.pw2.plane, tsize, (long long)ln.pw2.ntasks * nb)))
+    return PK_PWAVE2;
   if (!ln.pcube) return PK_PBLOCK;
-  if (ln.pwave) return PK_PWAVE;
-  return ln.pcube_stream && !clos ? PK_PCUBE_S : PK_PCUBE;
+  if (ln.pwave && pwave_pays(ln.pwave_nb, ln.pcb.N1, ln.pcb.plane, tsize, clos)) return PK_PWAVE;
+  return ln.pcube_s && !clos ? PK_PCUBE_S : PK_PCUBE;
 }
 
 // --------------------------------------------------------------------------
@@ -935,7 +941,7 @@ void launch_p(chfpe_ctx *c, const Batch &b, PKernel pk, const T *X, TO *out, con
 template <typename T, int EPI>
 void launch_stage(chfpe_ctx *c, const Batch &b, const T *X, T *t, const T *y, T *xo, double cst, int kind) {
   const Launch &ln = c->ln;
-  const PKernel pk = p_kernel(c, sizeof(T), c->closure_on);
+  const PKernel pk = p_kernel(c, b.g.nbatch, sizeof(T), c->closure_on);
   if (ln.hcube) {  // Hermite basis: the whole stage in one launch
     const int hk = EPI == EPI_H1 ? K_HS1 : EPI == EPI_H4 ? K_HS4 : EPI == EPI_OUT ? K_HOUT
                    : kind == K_QS3 ? K_HS3 : K_HS2;
@@ -981,7 +987,7 @@ void launch_perturb(chfpe_ctx *c, const double *W, TO *out, const double *grad) 
     hipLaunchKernelGGL((k_hperturb<TO>), dim3(2048), dim3(256), 0, c->stream, b.g, W, out, grad);
     return;
   }
-  launch_p<double, TO, true>(c, b, p_kernel(c, sizeof(double), c->closure_on), W, out, grad);
+  launch_p<double, TO, true>(c, b, p_kernel(c, 1, sizeof(double), c->closure_on), W, out, grad);
   if (c->ln.has_qx)
     launch_q_t<double, TO, false, EPI_ACC, FX, FQ>(c, b, b.qx, c->ln.qx_threads, 0, c->ln.qx_nmax, W, out,
                                                    nullptr, nullptr, grad, 0.0);
@@ -1572,9 +1578,9 @@ int chfpe_kernel_plan(const chfpe_params *p, int32_t *out, int32_t n) {
   for (int s = 0; s < d.M; ++s) clos = clos && d.Nq[s] <= 16 && d.Np[s] <= 16;
   const Launch &ln = c->ln;
   const size_t bsize = d.prec == CHFPE_FP32 ? sizeof(float) : sizeof(double);
-  const int32_t v[6] = {p_kernel(c.get(), sizeof(double), false),
-                        d.batched ? p_kernel(c.get(), bsize, false) : 0,
-                        clos ? p_kernel(c.get(), sizeof(double), true) : 0,
+  const int32_t v[6] = {p_kernel(c.get(), 1, sizeof(double), false),
+                        d.batched ? p_kernel(c.get(), d.B, bsize, false) : 0,
+                        clos ? p_kernel(c.get(), 1, sizeof(double), true) : 0,
                         d.hermite ? 0 : ln.qcube ? 2 : 1,
                         clos ? 1 : 0,
                         ln.one ? 1 : 0};
@@ -2053,7 +2059,7 @@ int chfpe_tile_config(const chfpe_ctx *c, int32_t *out, int32_t n) {
   const int32_t v[15] = {c->ln.pb.nb,  c->ln.pb.split,    c->ln.pb_threads,
                          c->ln.qf.pc,  c->ln.has_qa ? c->ln.qa.pc : 0, c->ln.qf_threads,
                          c->tune_pb_nb, c->tune_pb_split, c->tune_q_pc, c->ln.pb.run, c->tune_pb_run,
-                         c->ln.pcube ? 1 : 0, c->ln.pcube && c->ln.pcube_stream ? 1 : 0,
+                         c->ln.pcube ? 1 : 0, c->ln.pcube && (c->ln.pwave || c->ln.pcube_s) ? 1 : 0,
                          c->ln.hcube ? c->ln.hcb.chunk : 0, c->ln.hcube ? c->ln.hcb.ktile : 0};
   const int k = n < 15 ? n : 15;
   for (int i = 0; i < k; ++i) out[i] = v[i];

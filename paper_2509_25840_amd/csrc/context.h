@@ -62,8 +62,9 @@ struct Launch {
   bool has_qa = false, qf_two = false, has_qx = false;
   // three modes: all p axes of a q point in one k_pcube task (then the q
   // passes are (q_2, q_3) and q_1 alone, and excitations need no qx)
-  bool pcube = false, pcube_split = false, pcube_stream = false;
-  bool pwave = false;  // the streamed form is k_pwave (p axes of at most 24 points)
+  bool pcube = false, pcube_split = false;
+  bool pcube_s = false;  // k_pcube_s rather than k_pcube
+  bool pwave = false;    // k_pwave can take the block (p axes of at most 24 points), where it pays
   int pwave_nb = 0;
   // two modes: the p side by k_pwave2 (p axes of at most 32 points)
   bool pwave2 = false;
@@ -76,7 +77,7 @@ struct Launch {
   bool hcube = false;
   PCube hcb{};
   int hcube_threads = 0, hcube_nb1 = 0;
-  bool hwave = false;  // k_hwave (three modes, q axes of at most 24 points; two modes, 32)
+  bool hwave = false;  // k_hwave can take it (three modes, q axes of at most 24 points; two modes, 32)
   int hwave_nb = 0;
   int pcube_threads = 0, pcube_nb1 = 0;
   // one mode: whole propagations by one workgroup per state (k_one)
@@ -189,6 +190,57 @@ inline int pwave_nw(const PCube &p, int nb) {
   const bool exact = p.N1 == nb && p.N2 == nb && p.N3 == nb;
   const int per = wave_ps(nb, exact) * pwave_npw(nb, exact);
   return (p.N1 + per - 1) / per;
+}
+
+// Where k_pwave is the faster form of a block of n1 planes of `plane` points,
+// lines in the nb bucket; below, k_pcube (p_1 axes up to 16 points and no
+// closure: k_pcube_s).  A wave goes through its planes one by one, with all nb
+// steps of a line solve and all vectors of its variant however few lines and
+// points they have; k_pcube's cost follows the points in waves of 64.  RK4
+// steps at 504 q points and four elements, k_pcube[_s] and k_pwave, FP64 and
+// four FP32 states, in us:
+//   24 x 5 x 5   226  506,  392  757    24 x 13 x 13   802  794, 1866 1482
+//   24 x 10 x 10 505  652, 1038 1081    24 x 16 x 16  1112  986, 2461 2031
+//   24 x 12 x 11 682  727, 1620 1282    17 x 14 x 14   687  728, 1712 1426
+//   5 x 6 x 20   164  197,  326  312    5 x 7 x 20     230  225,  425  350
+//   16 x 8 x 8   223  233,  370  420    16 x 9 x 9     254  262,  500  489
+//   16 x 10 x 10 282  287,  565  534    13 x 11 x 11   277  275,  563  514
+//   12 x 8 x 8   196  200,  315  343    12 x 9 x 9     210  220,  418  394
+//   5 x 5 x 13   137  131,  251  208    8 x 5 x 5      123  103,  182  146
+// and with a closure 16 x 8 x 8 269 298, 16 x 9 x 9 380 329, 12 x 10 x 10 269
+// 281, 9 x 7 x 13 227 245, 5 x 11 x 13 287 237.
+inline bool pwave_pays(int nb, int n1, int plane, size_t tsize, bool clos) {
+  if (nb <= 8) return true;
+  if (clos) return plane > (nb == 16 && n1 > 12 ? 64 : 100);
+  if (nb <= 16) return plane > (tsize == 8 && n1 > 8 ? 90 : 64);
+  return plane > (tsize == 8 ? (n1 > 8 ? 200 : 128) : (n1 > 8 ? 128 : 96));
+}
+// The same for three-mode k_hwave and k_hcube, by the q cube: steps of 4 x 5 x 4
+// functions and ten elements, k_hcube and k_hwave, FP64 and four FP32 states:
+//   24 x 5 x 5   214  410,  249  746    24 x 13 x 13   328  445,  869  860
+//   24 x 16 x 16 684  456, 1028  917    17 x 14 x 14   467  384,  707  840
+//   12 x 10 x 20 204  229,  479  349    5 x 13 x 20    276  124,  358  224
+//   5 x 8 x 20   104  111,  188  199    16 x 7 x 7     174  172,  203  236
+//   13 x 8 x 8   161  167,  185  220    16 x 9 x 9     190  179,  339  248
+//   12 x 5 x 5   115   99,  137  155    12 x 8 x 8     145  102,  169  163
+inline bool hwave_pays(int nb, int n1, int plane, size_t tsize) {
+  if (nb <= 8) return true;
+  if (tsize == 8) return plane > (nb <= 12 ? 0 : nb <= 16 ? 48 : n1 > 16 ? 192 : 256);
+  return plane > (nb <= 12 ? 48 : nb <= 16 ? 64 : n1 > 16 ? 200 : n1 > 8 ? 128 : 160);
+}
+// Where k_pwave2 is the faster form for a launch of `tasks` planes: a task is a
+// wave however small its plane, and once there are several waves for every slot
+// of the device k_pblock packs small planes better.  RK4 steps of 20 x 24 q
+// points and six elements, k_pblock and k_pwave2, FP64: 25 x 5 points, one state
+// 88 79 us, 8 states 189 232, 32 states 716 904; 32 x 5, 1 and 16 states 96 83,
+// 451 507; 32 x 6, 99 86, 515 558; 25 x 8, 97 87, 565 550; 20 x 5, 82 73, 285
+// 307; 24 x 6, 88 76, 394 354; 8 x 8, 8 and 32 states 105 115, 229 288; 9 x 5, 1
+// and 16 states 70 62, 166 185 (FP32 142 151); 5 x 5, 70 61, 180 169 (148 134);
+// 13 x 5, 76 69, 248 233.  Larger planes of FP32 gain.
+inline bool pwave2_pays(int nb, int plane, size_t tsize, long long tasks) {
+  if (nb <= 12) return plane <= 32 || plane > 64 || tasks <= 16384;
+  if (nb <= 16 || tsize == 4) return true;
+  return plane > (nb <= 24 ? 120 : 196) || tasks <= 8192;
 }
 
 // Waves of a k_hwave workgroup, and its workgroups for ntasks tasks (two

@@ -23,7 +23,7 @@ void launch_pcube_s(chfpe_ctx *c, const Batch &b, const T *X, TO *out, const dou
     }
   }
   if constexpr (NB1 <= 32) {
-    if (c->ln.pcube_stream) {
+    if (c->ln.pcube_s) {
       launch_pcube_k(c, k_pcube_s<T, TO, NB1, PERTURB>, pcube_lds_bytes(c->d, sizeof(T), pad, true), b, X,
                      out, grad);
       return;

@@ -70,10 +70,17 @@ template <typename T, typename TO, int NB, bool PERTURB>
 void launch_pwave2_n(chfpe_ctx *c, const Batch &b, const T *X, TO *out, const double *grad) {
   constexpr int full = wave_nv(NB, 1, 1);
   if (b.pw2.N2 == NB && b.pw2.N3 == NB) return launch_pwave2_k<T, TO, NB, 0, PERTURB>(c, b, X, out, grad);
-  if constexpr (full >= 4) {
-    constexpr int part = (full * 5 + 7) / 8;  // planes well below NB x NB: fewer registers
+  // planes well below NB x NB: fewer registers and no loads of empty vectors (25 x
+  // 5 points, 16 FP64 states, with 10, 3 vectors a lane 524, 417 us an RK4 step;
+  // 32 x 8, one state, with 10, 5 101, 94; 9 x 5 with 3, 1 66, 62)
+  constexpr int part = (full * 5 + 7) / 8;
+  constexpr int small = NB >= 24 ? 3 : NB == 12 ? 1 : part, mid = NB >= 32 ? 5 : small;
+  if constexpr (small < part)
+    if (b.pw2.plane <= 64 * small) return launch_pwave2_k<T, TO, NB, small, PERTURB>(c, b, X, out, grad);
+  if constexpr (mid > small)
+    if (b.pw2.plane <= 64 * mid) return launch_pwave2_k<T, TO, NB, mid, PERTURB>(c, b, X, out, grad);
+  if constexpr (full >= 4)
     if (b.pw2.plane <= 64 * part) return launch_pwave2_k<T, TO, NB, part, PERTURB>(c, b, X, out, grad);
-  }
   launch_pwave2_k<T, TO, NB, full, PERTURB>(c, b, X, out, grad);
 }
 

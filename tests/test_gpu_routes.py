@@ -1,0 +1,142 @@
+"""Results on either side of the lines between kernels of the same work: the
+shapes of test_plan.py, whose kernels that file asserts, against the oracles,
+and waves of branches against the FP64 responses of single states.
+
+Tolerances: FP64 as in the other parity tests (a few hundred products per value
+and two RK4 steps: 1e-13; 200 steps of a bounded propagation by another
+kernel: 1e-11).  FP32 branches round every value four times a step, 6e-8 each:
+at most 5e-5 after the 200 steps of a branch here, below the FP32 bar of 1e-4.
+(The times are long enough for R to develop: at t near 0 it is a difference of
+far larger terms.)
+"""
+import numpy as np
+import pytest
+
+import oracle as orc
+import oracle.closure as cl
+import oracle.hermite as oh
+import test_plan
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-13
+X3 = {"lin": [1.0, -0.7, 0.4], "quad": [[0.2, 0.05, -0.03], [0.05, -0.1, 0.02], [-0.03, 0.02, 0.3]]}
+
+
+def rel_l2(a, b):
+    a, b = np.asarray(a, dtype=np.float64).ravel(), np.asarray(b, dtype=np.float64).ravel()
+    return float(np.linalg.norm(a - b) / np.linalg.norm(b))
+
+
+def ops(M):
+    return {"lin": X3["lin"][:M], "quad": [r[:M] for r in X3["quad"][:M]]}
+
+
+def grid_state(w, seed):
+    sm = wl.smooth_state(w, seed=seed)
+    return orc.boltzmann(w)[0][None] * (1.0 + 0.3 * sm / np.abs(sm).max() + 0.05 * wl.noise_state(w, seed=seed + 1))
+
+
+@pytest.fixture(scope="module")
+def pk():
+    import torch
+    import paper_2509_25840_amd as pk
+    assert torch.cuda.is_available(), "GPU tests need a visible GPU"
+    return pk
+
+
+def check_waves(pk, w, batch=2, n_t1=3, prec=1):
+    """Branch waves (the last one ragged) against the response of single states."""
+    M = w["M"]
+    A, B = ops(M), wl.optical(M, lin=[0.5, 0.8, -0.3][:M])
+    R = {}
+    for key, kw in (("one", {}), ("wave", {"precision": prec, "batch": batch})):
+        with pk.Solver(pk.params_from_workload(w, **kw)) as s:
+            s.equilibrate(20, 0.005)
+            R[key] = s.response_2d(A, B, A, n_t1, 6, 40 // n_t1 + 1, 40, 0.005)
+    e = rel_l2(R["wave"], R["one"])
+    print(f"    waves {e:.2e} of {np.abs(R['one']).max():.1e}", flush=True)
+    assert e < (1e-4 if prec else 1e-11)
+
+
+@pytest.mark.parametrize("Np", [c[0] for c in test_plan.THREE], ids=str)
+def test_three_modes(pk, Np):
+    print(f"[three modes] p {Np}", flush=True)
+    w = wl.workload("three_mode_24", Nq=[5, 6, 5], Np=list(Np), K=1)
+    W = grid_state(w, 3)
+    with pk.Solver(pk.params_from_workload(w)) as s:
+        s.set_state(W)
+        s.rhs()
+        e_rhs = rel_l2(s.get_state(), orc.rhs(w, W))
+        s.set_state(W)
+        s.propagate(2, 0.002)
+        e_rk4 = rel_l2(s.get_state(), orc.rk4(w, W, 2, 0.002))
+        s.set_state(W)
+        s.perturb(X3)
+        e_x = rel_l2(s.get_state(), orc.perturb(w, X3, W))
+    print(f"    rhs {e_rhs:.2e} rk4 {e_rk4:.2e} perturb {e_x:.2e}", flush=True)
+    assert e_rhs < TOL and e_rk4 < TOL and e_x < TOL
+    check_waves(pk, w)
+
+
+@pytest.mark.parametrize("Np", [c[0] for c in test_plan.THREE if c[3]], ids=str)
+def test_three_modes_with_a_closure(pk, Np):
+    print(f"[closure] p {Np}", flush=True)
+    w = wl.workload("three_mode_24", Nq=[5, 6, 5], Np=list(Np), K=1)
+    sv = np.random.default_rng(9).normal(0, 0.02, len(cl.features(w)))
+    W = grid_state(w, 5)
+    with pk.Solver(pk.params_from_workload(w)) as s:
+        s.set_closure(sv)
+        s.set_state(W)
+        s.propagate(2, 0.002)
+        e_rk4 = rel_l2(s.get_state(), cl.propagate(w, W, 2, 0.002, sv))
+        s.set_state(W)
+        s.perturb(X3)
+        e_x = rel_l2(s.get_state(), cl.perturb(w, X3, W, sv))
+    print(f"    rk4 {e_rk4:.2e} perturb {e_x:.2e}", flush=True)
+    assert e_rk4 < TOL and e_x < TOL
+
+
+@pytest.mark.parametrize("Nq", [c[0] for c in test_plan.HERMITE], ids=str)
+def test_hermite_basis(pk, Nq):
+    M = len(Nq)
+    print(f"[hermite] q {Nq}", flush=True)
+    w = wl.workload({1: "one_mode_48", 2: "two_mode_32", 3: "three_mode_24"}[M], Nq=list(Nq), Np=[3, 2, 2][:M], K=2,
+                    basis="hermite")
+    rng = np.random.default_rng(8)
+    qs = np.meshgrid(*[oh.q_grid(w, s) for s in range(M)], indexing="ij")
+    env = np.exp(-0.35 * sum((w["omega"][s] * qs[s]) ** 2 for s in range(M)))
+    C = rng.normal(size=oh.shape(w)[:1 + M] + (1,) * M) * env * (1.0 + 0.1 * rng.normal(size=oh.shape(w)))
+    T = oh.tables(w)
+    with pk.Solver(pk.params_from_workload(w)) as s:
+        s.set_state(C)
+        s.rhs()
+        e_rhs = rel_l2(s.get_state(), oh.rhs(w, C, T))
+        s.set_state(C)
+        s.propagate(2, 0.002)
+        e_rk4 = rel_l2(s.get_state(), oh.rk4(w, C, 2, 0.002, T))
+    print(f"    rhs {e_rhs:.2e} rk4 {e_rk4:.2e}", flush=True)
+    assert e_rhs < TOL and e_rk4 < TOL
+    check_waves(pk, w)
+
+
+# planes of one, three and five vectors a lane, and waves of more and fewer states
+# than k_pblock takes over at
+@pytest.mark.parametrize("Np,batch,prec", [((9, 5), 2, 1), ((20, 5), 2, 1), ((24, 8), 2, 1), ((32, 5), 2, 1),
+                                           ((32, 8), 2, 1), ((25, 12), 2, 0), ((27, 17), 2, 1), ((8, 8), 24, 0),
+                                           ((8, 8), 24, 1), ((5, 5), 24, 0), ((25, 5), 12, 0), ((20, 6), 12, 0)], ids=str)
+def test_two_modes(pk, Np, batch, prec):
+    print(f"[two modes] p {Np}, {batch} states", flush=True)
+    w = wl.workload("two_mode_32", Nq=[9, 9], Np=list(Np), K=3)
+    W = grid_state(w, 3)
+    with pk.Solver(pk.params_from_workload(w)) as s:
+        s.set_state(W)
+        s.propagate(2, 0.002)
+        e_rk4 = rel_l2(s.get_state(), orc.rk4(w, W, 2, 0.002))
+        s.set_state(W)
+        s.perturb(ops(2))
+        e_x = rel_l2(s.get_state(), orc.perturb(w, ops(2), W))
+    print(f"    rk4 {e_rk4:.2e} perturb {e_x:.2e}", flush=True)
+    assert e_rk4 < TOL and e_x < TOL
+    check_waves(pk, w, batch=batch, n_t1=batch + 1, prec=prec)

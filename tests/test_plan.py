@@ -45,6 +45,56 @@ def test_three_mode_q_cubes(plan, N):
     assert plan(3, [N] * 3, (5, 5, 7))["q"] == "k_qpass"  # 175 p points: no whole 16-byte vectors
 
 
+# (p axes, FP64 state, FP32 branches, FP64 state with a closure): planes on either
+# side of each line between k_pwave and k_pcube, and axes that only k_pcube_s takes
+THREE = [((24, 5, 5), "k_pcube", "k_pcube", ""), ((24, 13, 13), "k_pcube", "k_pwave", ""),
+         ((24, 16, 16), "k_pwave", "k_pwave", ""), ((17, 12, 10), "k_pcube", "k_pcube", ""),
+         ((5, 6, 20), "k_pcube_s", "k_pwave", ""), ((5, 5, 18), "k_pcube_s", "k_pcube_s", ""),
+         ((5, 7, 20), "k_pwave", "k_pwave", ""), ((16, 8, 8), "k_pcube_s", "k_pcube_s", "k_pcube"),
+         ((16, 9, 9), "k_pcube_s", "k_pwave", "k_pwave"), ((13, 11, 11), "k_pwave", "k_pwave", "k_pwave"),
+         ((12, 8, 8), "k_pcube_s", "k_pcube_s", "k_pcube"), ((12, 10, 10), "k_pwave", "k_pwave", "k_pcube"), ((12, 10, 9), "k_pcube_s", "k_pwave", "k_pcube"),
+         ((5, 5, 13), "k_pwave", "k_pwave", "k_pcube"), ((8, 5, 5), "k_pwave", "k_pwave", "k_pwave"),
+         ((12, 12, 12), "k_pwave", "k_pwave", "k_pwave"), ((8, 5, 26), "k_pcube_s", "k_pcube_s", ""),
+         ((16, 26, 9), "k_pcube_s", "k_pcube_s", ""), ((20, 7, 25), "k_pcube", "k_pcube", "")]
+
+
+@pytest.mark.parametrize("Np,f64,f32,clos", THREE)
+def test_three_modes(plan, Np, f64, f32, clos):
+    got = plan(3, (5, 6, 5), Np, precision=1, batch=2)
+    assert (got["state"], got["branches"]) == (f64, f32)
+    got = plan(3, (5, 6, 5), Np)
+    assert (got["state"], got["branches"], got["closure"]) == (f64, "", clos)
+    left = plan(3, (5, 6, 5), Np, precision=1, batch=2, CHFPE_PWAVE=0)
+    assert left["state"] == left["branches"] == ("k_pcube_s" if Np[0] <= 16 else "k_pcube")
+
+
+# (q axes, FP64 state, FP32 branches): as above for k_hwave and k_hcube
+HERMITE = [((24, 5, 5), "k_hcube", "k_hcube"), ((24, 13, 13), "k_hcube", "k_hcube"), ((24, 16, 16), "k_hwave", "k_hwave"),
+           ((17, 14, 14), "k_hwave", "k_hcube"), ((12, 10, 20), "k_hcube", "k_hwave"), ((5, 13, 20), "k_hwave", "k_hwave"),
+           ((16, 7, 7), "k_hwave", "k_hcube"), ((16, 6, 6), "k_hcube", "k_hcube"), ((13, 9, 9), "k_hwave", "k_hwave"),
+           ((12, 5, 5), "k_hwave", "k_hcube"), ((12, 8, 8), "k_hwave", "k_hwave"), ((8, 5, 5), "k_hwave", "k_hwave"),
+           ((32, 8, 9), "k_hcube", "k_hcube"), ((6, 27, 7), "k_hcube", "k_hcube"), ((40, 20), "k_hcube", "k_hcube"),
+           ((33, 9), "k_hcube", "k_hcube"), ((5, 5), "k_hwave", "k_hwave"), ((32, 5), "k_hwave", "k_hwave"),
+           ((31,), "k_hcube", "k_hcube")]
+
+
+@pytest.mark.parametrize("Nq,f64,f32", HERMITE)
+def test_hermite_basis(plan, Nq, f64, f32):
+    got = plan(len(Nq), Nq, (3, 2, 2)[:len(Nq)], precision=1, batch=2, basis="hermite")
+    assert (got["state"], got["branches"], got["q"]) == (f64, f32, "")
+    left = plan(len(Nq), Nq, (3, 2, 2)[:len(Nq)], precision=1, batch=2, basis="hermite", CHFPE_HWAVE=0)
+    assert left["state"] == left["branches"] == "k_hcube"
+
+
+@pytest.mark.parametrize("Np,prec,batch,branches", [
+    ((8, 8), 0, 9, "k_pwave2"), ((8, 8), 0, 64, "k_pblock"), ((8, 8), 1, 64, "k_pblock"), ((5, 5), 0, 64, "k_pwave2"),
+    ((13, 5), 0, 64, "k_pwave2"), ((25, 5), 0, 16, "k_pblock"), ((25, 5), 1, 16, "k_pwave2"), ((24, 6), 0, 16, "k_pwave2"),
+    ((20, 6), 0, 16, "k_pblock"), ((32, 6), 0, 16, "k_pblock"), ((28, 8), 0, 16, "k_pwave2"), ((32, 5), 0, 3, "k_pwave2")])
+def test_two_mode_waves_of_small_planes(plan, Np, prec, batch, branches):
+    got = plan(2, (20, 24), Np, precision=prec, batch=batch)
+    assert (got["state"], got["branches"]) == ("k_pwave2", branches)
+
+
 def test_one_mode(plan):
     cases = next(m for m in test_gpu_one.test_steps_and_response_match_the_oracle.pytestmark if m.name == "parametrize")
     for Nq, Np, K in cases.args[1]:
