@@ -52,3 +52,16 @@ def test_two_threads_with_a_solver_each(pk):
     for x in t:
         x.join()
     assert not bad
+
+
+def test_pinned_arrays_come_back_as_they_went_in(pk):
+    """Arrays that the caller has pinned go over the link directly."""
+    import torch
+    with solver(pk, [32, 32], [24, 16], 5) as s:
+        a = torch.empty(s.count, dtype=torch.float64, pin_memory=True).numpy()
+        b = torch.empty(s.count, dtype=torch.float64, pin_memory=True).numpy()
+        for seed in (0, 1):
+            a[:] = np.random.default_rng(seed).normal(size=s.count)
+            s.set_state(a)
+            s._check(pk.lib().chfpe_get_state(s._ctx, pk._dptr(b)))
+            assert np.array_equal(a, b) and np.array_equal(s.get_state(), a)
