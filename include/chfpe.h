@@ -305,8 +305,11 @@ int chfpe_kernel_times(chfpe_ctx *ctx, int32_t max_kinds, int64_t *counts, doubl
  * (positions of the contiguous run per two-axis tile, as LDS allows) with
  * the best k_pblock shape, then the k_pblock task order (runs of 1, 4, 8,
  * 16, 32 consecutive block groups of one state before the next element).
- * Candidates whose launch would exceed one dispatch are skipped.  Every
- * candidate computes the same result.  The path timed is the one the context spends
+ * Candidates whose launch would exceed one dispatch are skipped, and so are
+ * those that change no launch of the step (the widths where k_qcube takes the
+ * q side, lane pairs where k_pwave takes the p side); one-mode contexts that
+ * run k_one, and the Hermite basis, have nothing to choose and return at once.
+ * Every candidate computes the same result.  The path timed is the one the context spends
  * most time in: the batched branch buffers (branch type) when batch > 1,
  * else the FP64 single-state path.  The fastest shape is kept by this
  * context and, for the rest of the process, by every later context of the

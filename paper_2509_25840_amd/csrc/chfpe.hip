@@ -924,6 +924,9 @@ Batch batch_of(const chfpe_ctx *c, int nb) {
   return b;
 }
 
+// The q side in one pass (a closure keeps the separate ones).
+bool use_qcube_now(const chfpe_ctx *c) { return c->ln.qcube && !c->closure_on; }
+
 // p side of a right-hand side, or of an excitation (PERTURB), by kernel pk
 template <typename T, typename TO, bool PERTURB>
 void launch_p(chfpe_ctx *c, const Batch &b, PKernel pk, const T *X, TO *out, const double *grad) {
@@ -956,7 +959,7 @@ void launch_stage(chfpe_ctx *c, const Batch &b, const T *X, T *t, const T *y, T 
     TimedScope ts(c, ln.pcube ? K_PCUBE : K_PBLOCK, b.g.nbatch, sizeof(T));
     launch_p<T, T, false>(c, b, pk, X, t, nullptr);
   }
-  if (ln.qcube && !c->closure_on) {
+  if (use_qcube_now(c)) {
     TimedScope ts(c, kind, b.g.nbatch, sizeof(T));
     launch_qcube<T>(c, b, X, t, y, xo, cst, EPI);
     return;
@@ -1985,7 +1988,8 @@ int chfpe_set_kernel_timing(chfpe_ctx *c, int32_t every) {
 int chfpe_autotune(chfpe_ctx *c, int32_t n_steps) {
   if (!c) return CHFPE_EINVAL;
   if (n_steps < 1 || n_steps > 1000) return fail(c, CHFPE_EINVAL, "need 1 <= n_steps <= 1000");
-  if (c->d.hermite) return CHFPE_OK;  // one k_hcube shape: nothing to choose
+  // nothing to choose: a Hermite stage, and whole propagations in k_one, have one shape
+  if (c->d.hermite || (c->ln.one && !c->closure_on)) return CHFPE_OK;
   const Derived &d = c->d;
   // the timed steps run on scratch buffers holding zeros (the work does not
   // depend on the values); the cached wave graph holds the old tile shapes
@@ -2016,11 +2020,17 @@ int chfpe_autotune(chfpe_ctx *c, int32_t n_steps) {
     c->tune_q_pc = t.q_pc;
     c->tune_pb_run = t.pb_run;
     if (!plan(c)) return CHFPE_OK;  // too large a launch for one dispatch: not a candidate
-    const int split = c->ln.pwave ? 0 : c->ln.pb.split;  // (k_pwave has one line solve)
-    const std::vector<int> eff = {c->ln.pb.nb, split, c->ln.qf.pc, c->ln.qa.pc, c->ln.pb.run,
-                                  c->ln.pwave2};
+    // what the timed launches are: a request that changes none of them is not
+    // timed, nor kept (equal launches would be told apart by noise alone)
+    const Launch &ln = c->ln;
+    const PKernel pk = p_kernel(c, d.batched ? d.B : 1, d.prec == CHFPE_FP32 ? sizeof(float) : sizeof(double),
+                                c->closure_on);
+    std::vector<int> eff = {pk};
+    if (pk == PK_PBLOCK) eff.insert(eff.end(), {ln.pb.nb, ln.pb.split, ln.pb.run});
+    if (pk == PK_PCUBE) eff.push_back(ln.pcube_split);
+    if (!use_qcube_now(c)) eff.insert(eff.end(), {ln.qf.pc, ln.has_qa ? ln.qa.pc : 0});
     for (const auto &s : seen)
-      if (s == eff) return CHFPE_OK;  // same launches as a shape already timed
+      if (s == eff) return CHFPE_OK;
     seen.push_back(eff);
     const double ms = time_rk4_step(c, n_steps, dt);
     if (ms < 0) return CHFPE_EDEVICE;
