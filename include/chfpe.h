@@ -287,7 +287,9 @@ int chfpe_stream_mix(void *dst, const void *a, const void *b, const void *c, int
 /* Per-kernel timing with HIP events on the context's stream: every
  * `every`-th RK4 step (0 turns timing off) each launch of that step is
  * bracketed by events; while timing is on, 2D-response waves are issued
- * directly instead of as HIP graphs.  chfpe_kernel_times reports, for each
+ * directly instead of as HIP graphs.  Results do not depend on it.  One-mode
+ * contexts that propagate in single launches (k_one, up to 256 steps each, kind
+ * "one_propagation") bracket each launch that holds such a step.  chfpe_kernel_times reports, for each
  * kernel kind, the number of timed launches, their mean duration in
  * milliseconds, their mean algorithmic bytes (each input state read once and
  * each output state written once) and the kind's name; launches that carry

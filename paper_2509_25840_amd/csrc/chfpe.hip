@@ -61,20 +61,26 @@ enum Kind : int {
   K_HS2 = 11,
   K_HS3 = 12,
   K_HS4 = 13,
-  K_HOUT = 14
+  K_HOUT = 14,
+  K_ONE = kNumBase  // whole propagations, after the kinds of single passes; K_ONE + 1 for several states
 };
+int kind_of(int k, int nstates) {
+  if (k == K_ONE) return 2 * kNumBase + (nstates > 1 ? 1 : 0);
+  return k + (nstates > 1 ? kNumBase : 0);
+}
 const char *kKindNames[kNumKinds] = {
     "pblock_rhs", "qpass_acc", "qpass_rk4_s1", "qpass_rk4_s2", "qpass_rk4_s3", "qpass_rk4_s4", "observe",
     "perturb", "qpass_out", "pcube_rhs", "hcube_rk4_s1", "hcube_rk4_s2", "hcube_rk4_s3", "hcube_rk4_s4",
     "hcube_out", "batch_pblock_rhs", "batch_qpass_acc", "batch_qpass_rk4_s1",
     "batch_qpass_rk4_s2", "batch_qpass_rk4_s3", "batch_qpass_rk4_s4", "batch_observe", "batch_perturb",
     "batch_qpass_out", "batch_pcube_rhs", "batch_hcube_rk4_s1", "batch_hcube_rk4_s2", "batch_hcube_rk4_s3",
-    "batch_hcube_rk4_s4", "batch_hcube_out"};
+    "batch_hcube_rk4_s4", "batch_hcube_out", "one_propagation", "batch_one_propagation"};
 // state passes each kind reads plus writes (each input once, each output
 // once): the first stage reads its input (y) and t and writes z1; later
 // stages also read y (the last one reads and writes it in place); a
-// Hermite stage reads its input (and y) and writes its output
-const double kKindPasses[kNumBase] = {2, 3, 3, 4, 4, 4, 0.1, 2, 3, 2, 2, 3, 3, 3, 2};
+// Hermite stage reads its input (and y) and writes its output; a k_one launch
+// reads and writes the state, whatever the number of steps in between
+const double kKindPasses[kNumBase + 1] = {2, 3, 3, 4, 4, 4, 0.1, 2, 3, 2, 2, 3, 3, 3, 2, 2};
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
@@ -878,7 +884,7 @@ struct TimedScope {
   double bytes;
   hipEvent_t a = nullptr;
   TimedScope(chfpe_ctx *c_, int k, int nstates = 1, size_t tsize = sizeof(double))
-      : c(c_), kind(k + (nstates > 1 ? kNumBase : 0)),
+      : c(c_), kind(kind_of(k, nstates)),
         bytes(kKindPasses[k] * (double)nstates * (double)c_->d.S * (double)tsize) {
     if (c->timing_now && !c->capturing) {
       a = get_event(c);
@@ -1002,9 +1008,50 @@ int last_launch_error(chfpe_ctx *c) {
   return CHFPE_OK;
 }
 
-// One mode: k_one instead of the launches of single stages (which kernel
-// timing and a closure keep).
-bool use_one(const chfpe_ctx *c) { return c->ln.one && c->timing_every == 0 && !c->closure_on; }
+// One mode: k_one instead of the launches of single stages (a closure keeps those).
+bool use_one(const chfpe_ctx *c) { return c->ln.one && !c->closure_on; }
+
+// RK4 steps of one k_one launch: a few milliseconds, so that no launch of a long
+// propagation holds its compute unit for seconds.
+constexpr long long kOneSteps = 256;
+
+// nb states propagated by n_samples times `stride` RK4 steps (none before the
+// first sample if `first`); R (may be null) receives <C> of state b after sample
+// j at j * ostride + b * bstride.
+template <typename T>
+int run_one(chfpe_ctx *c, int nb, T *states, long long n_samples, long long stride, bool first, double dt, double *R,
+            long long ostride, int bstride) {
+  auto go = [&](bool f, long long n, long long steps, double *out) {
+    const long long total = (n - (f ? 1 : 0)) * steps, to = c->step_counter + total;
+    // timed where one of its steps would be
+    c->timing_now = c->timing_every > 0 && (to + c->timing_every - 1) / c->timing_every >
+                                               (c->step_counter + c->timing_every - 1) / c->timing_every;
+    c->step_counter = to;
+    {
+      TimedScope ts(c, K_ONE, nb, sizeof(T));
+      launch_one<T>(c, nb, states, n, steps, f, dt, out, ostride, bstride);
+    }
+    c->timing_now = false;
+  };
+  for (long long j = 0; j < n_samples;) {
+    long long left = j == 0 && first ? 0 : stride;
+    for (; left > kOneSteps; left -= kOneSteps) go(false, 1, kOneSteps, nullptr);
+    // further samples with this one, as far as the step limit allows
+    const long long more =
+        stride > kOneSteps ? 0 : std::min(n_samples - j - 1, (kOneSteps - left) / std::max(1LL, stride));
+    double *out = R ? R + j * ostride : nullptr;
+    if (more > 0)
+      go(left == 0, more + 1, stride, out);
+    else
+      go(left == 0, 1, left, out);
+    j += 1 + more;
+    if (c->pending.size() > 4096) {
+      int rc = drain_timing(c);
+      if (rc) return rc;
+    }
+  }
+  return last_launch_error(c);
+}
 
 // The buffers of one RK4 integration: y (in place), the alternating stage
 // states xa/xb, and the partial right-hand side t.
@@ -1018,7 +1065,7 @@ struct RK4Bufs {
 template <typename T>
 int rk4(chfpe_ctx *c, const Batch &b, const RK4Bufs<T> &r, long long nsteps, double dt) {
   if (use_one(c)) {
-    if (nsteps > 0) launch_one<T>(c, b.g.nbatch, r.y, 1, nsteps, false, dt, nullptr, 0, 0);
+    if (nsteps > 0) return run_one<T>(c, b.g.nbatch, r.y, 1, nsteps, false, dt, nullptr, 0, 0);
     return last_launch_error(c);
   }
   for (long long st = 0; st < nsteps; ++st) {
@@ -1072,10 +1119,7 @@ int observe_to(chfpe_ctx *c, const double *W, double *dst) {
 template <typename T>
 int sample(chfpe_ctx *c, const Batch &b, const RK4Bufs<T> &r, long long n, int stride, double dt, double *dst,
            long long ostride) {
-  if (use_one(c)) {
-    launch_one<T>(c, b.g.nbatch, r.y, n, stride, true, dt, dst, ostride, 1);
-    return last_launch_error(c);
-  }
+  if (use_one(c)) return run_one<T>(c, b.g.nbatch, r.y, n, stride, true, dt, dst, ostride, 1);
   for (long long j = 0; j < n; ++j) {
     if (j > 0) {
       int rc = rk4<T>(c, b, r, stride, dt);

@@ -21,7 +21,7 @@ namespace chfpe {
 
 constexpr int kPBlockRPT = 4;        // rows per k_pblock thread
 constexpr int kNumBase = 15;         // kernel kinds of the event timing (see Kind in chfpe.hip)
-constexpr int kNumKinds = 2 * kNumBase;
+constexpr int kNumKinds = 2 * kNumBase + 2;
 
 struct Derived {
   int prec = 0, B = 1;    // precision of branch states; branches per wave

@@ -27,7 +27,7 @@ template <typename T, int EPI>
 void launch_hcube(chfpe_ctx *c, const Batch &b, const T *X, const T *y, T *xo, double cst);
 template <typename T>
 void launch_hwave(chfpe_ctx *c, const Batch &b, const T *X, const T *y, T *xo, double cst, int epi);
-// One mode: nb states propagated by n_samples times `stride` RK4 steps (none
+// k_one: nb states propagated by n_samples times `stride` RK4 steps (none
 // before the first sample if `first`); R (may be null) receives <C> of state b
 // after sample j at j * ostride + b * bstride.
 template <typename T>
