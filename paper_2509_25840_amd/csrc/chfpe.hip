@@ -577,7 +577,10 @@ void plan_two(chfpe_ctx *c, int a, int b, int run, std::vector<int> rest, QPass 
     // -> 4.34, 24^2 FP32 2.4 -> 2.8; 24^2 FP64 gains 0 to 10%, left with FP32.
     const int fill = nmax_bucket(std::max(Na, Nb));
     const bool part = b < d.M && (fill == 24 || fill == 32) && (Na != fill || Nb != fill);
-    if (uneven || part) out = half;
+    // (its launch over every state must fit one dispatch too: threads come in whole
+    // waves, so that two half-width tasks can have more than a wide one)
+    const int half_thr = (std::max(Na, Nb) * half.pc + 63) / 64 * 64;
+    if ((uneven || part) && grid_items(half.ntasks * nbat, half_thr) <= kMaxGridItems) out = half;
   }
   thr = (std::max(Na, Nb) * out.pc + 63) / 64 * 64;
   lds = (size_t)Na * (Nb + 1) * out.pc * sizeof(double);

@@ -105,6 +105,15 @@ def test_one_mode(plan):
     assert plan(1, [20], [18], 3)["one"]
 
 
+@pytest.mark.parametrize("Nq,K,batch", [((5, 17), 11, 1024), ((5, 17), 12, 900), ((17, 5), 11, 1024), ((5, 26), 10, 900),
+                                        ((5, 18), 12, 900)])
+def test_half_width_q_tiles_refuse_no_batch(plan, Nq, K, batch):
+    """FP32 waves of 251 to 286 GB whose (q_1, q_2) launch fits one dispatch (2^32
+    work-items) with tiles of 16 positions, and would not with 8."""
+    assert plan(2, Nq, (48, 48), K, precision=1, batch=batch)["branches"] == "k_pcube"
+    assert plan(2, Nq, (48, 48), K, precision=1, batch=batch, CHFPE_TUNE_Q_PC=16)["branches"] == "k_pcube"
+
+
 def test_the_plan_is_refused_where_setup_refuses(plan):
     import paper_2509_25840_amd as pk
     with pytest.raises(pk.ChfpeError):
