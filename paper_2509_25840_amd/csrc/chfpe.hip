@@ -2345,7 +2345,7 @@ int chfpe_closure_train(const float *feat, int32_t rows, int32_t n_groups, const
   DevScratch ds;
   const size_t pieces[] = {(size_t)rows * kClosFeat * sizeof(float), (size_t)rows * kClosFeat * sizeof(short),
                            (size_t)prows * kClosFeat * sizeof(short), n_groups * sizeof(ClosGroup),
-                           gtot * sizeof(double), gtot * sizeof(double), rows * sizeof(double),
+                           gtot * sizeof(double), rows * sizeof(double),
                            n_groups * sizeof(double), 2 * sizeof(ClosState), sizeof(ClosParts), prows * sizeof(float),
                            prows * sizeof(float), (size_t)prows * kClosHid * sizeof(float), n_steps * sizeof(float)};
   size_t total = 0;
@@ -2354,13 +2354,12 @@ int chfpe_closure_train(const float *feat, int32_t rows, int32_t n_groups, const
   short *dfeat = upload_features(ds, feat, rows, st);
   short *dfeatT = ds.get<short>((size_t)prows * kClosFeat);
   ClosGroup *dgroups = ds.get<ClosGroup>(n_groups);
-  double *dG = ds.get<double>(gtot), *dGT = ds.get<double>(gtot), *db = ds.get<double>(rows),
-         *dlp = ds.get<double>(n_groups);
+  double *dG = ds.get<double>(gtot), *db = ds.get<double>(rows), *dlp = ds.get<double>(n_groups);
   ClosState *dnet = ds.get<ClosState>(2);
   ClosParts *dparts = ds.get<ClosParts>(1);
   float *dsv = ds.get<float>(prows), *dgsv = ds.get<float>(prows), *da1 = ds.get<float>((size_t)prows * kClosHid),
         *dl = ds.get<float>(std::max(1, n_steps));
-  if (!dfeat || !dfeatT || !dgroups || !dG || !dGT || !db || !dlp || !dnet || !dparts || !dsv || !dgsv || !da1 || !dl)
+  if (!dfeat || !dfeatT || !dgroups || !dG || !db || !dlp || !dnet || !dparts || !dsv || !dgsv || !da1 || !dl)
     return fail_g(CHFPE_ENOMEM, "closure train scratch");
   ClosState host;
   std::copy_n(prm, kClosParams, host.p[0]);
@@ -2372,14 +2371,14 @@ int chfpe_closure_train(const float *feat, int32_t rows, int32_t n_groups, const
   if (!up(dgroups, groups.data(), n_groups * sizeof(ClosGroup)) || !up(dG, G, gtot * sizeof(double)) ||
       !up(db, b, rows * sizeof(double)) || !up(dnet, &host, sizeof host))
     return fail_g(CHFPE_EDEVICE, "closure train upload");
-  hipLaunchKernelGGL(k_transpose_groups, dim3(n_groups), dim3(256), 0, st, dG, dGT, dgroups);
+  hipLaunchKernelGGL(k_transpose_groups, dim3(n_groups), dim3(256), 0, st, dG, dgroups);
   hipLaunchKernelGGL(k_transpose_features, dim3((prows * kClosFeat + 255) / 256), dim3(256), 0, st, dfeat, dfeatT,
                      (int)rows);
   for (int step = 0; step <= n_steps; ++step) {
     const bool last = step == n_steps;  // the last update
     hipLaunchKernelGGL(k_clos_step, dim3(last ? 1 : n_groups), dim3(64 * kStepWaves), 0, st,
                        dnet + (step ? (step + 1) % 2 : 0), dnet + step % 2, dparts, (int)adam_t0, step, last ? 1 : 0,
-                       lr, dfeat, (int)rows, dgroups, (int)n_groups, dGT, db, dsv, dgsv, da1, dlp);
+                       lr, dfeat, (int)rows, dgroups, (int)n_groups, dG, db, dsv, dgsv, da1, dlp);
     if (!last)
       hipLaunchKernelGGL(k_clos_parts, dim3(kPartsBlocks), dim3(64), 0, st, dnet + step % 2, dfeatT, (int)rows, da1,
                          dgsv, dlp, (int)n_groups, dparts, dl + step);

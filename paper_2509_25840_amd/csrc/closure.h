@@ -467,21 +467,25 @@ k_clos_grad(const float *__restrict__ prm, const short *__restrict__ feat, const
 
 // Training problem: rows grouped by (draw, axis); a group owns the P rows of
 // its entries, i0 .. i0 + P - 1, and the quadratic (G, b, c, t): GT[g + f P + e]
-// is G[e][f], b one value per row.
+// is G[e][f] (G transposed in place), b one value per row.
 struct ClosGroup {
   long long g;
   int i0, P;
   double c, t;
 };
 
-// GT = every group's P x P matrix transposed (one workgroup per group), so
+// Transposes every group's P x P matrix in place (one workgroup per group), so
 // that the rows of a group read consecutive values.
 __global__ void __launch_bounds__(256)
-k_transpose_groups(const double *__restrict__ G, double *__restrict__ GT, const ClosGroup *__restrict__ groups) {
+k_transpose_groups(double *__restrict__ G, const ClosGroup *__restrict__ groups) {
   const ClosGroup q = groups[blockIdx.x];
   for (long long v = threadIdx.x; v < (long long)q.P * q.P; v += blockDim.x) {
     const long long f = v / q.P, e = v - f * q.P;
-    GT[q.g + v] = G[q.g + e * q.P + f];
+    if (e <= f) continue;  // each pair once
+    const long long a = q.g + v, b = q.g + e * q.P + f;
+    const double x = G[a];
+    G[a] = G[b];
+    G[b] = x;
   }
 }
 
