@@ -140,3 +140,53 @@ def test_two_modes(pk, Np, batch, prec):
     print(f"    rk4 {e_rk4:.2e} perturb {e_x:.2e}", flush=True)
     assert e_rk4 < TOL and e_x < TOL
     check_waves(pk, w, batch=batch, n_t1=batch + 1, prec=prec)
+
+
+# FP32 branches by every form of the wave-plane kernels: cubes (16-byte vectors)
+# of each line bucket, and the vector counts of ragged planes
+PWAVE32 = [(8, 8, 8), (12, 12, 12), (16, 16, 16), (24, 24, 24), (7, 5, 6), (9, 12, 11), (13, 8, 16), (9, 15, 16),
+           (12, 7, 20), (5, 16, 24), (23, 24, 17)]
+HWAVE32 = [(8, 8, 8), (12, 12, 12), (16, 16, 16), (24, 24, 24), (5, 6, 7), (9, 12, 11), (7, 9, 16), (5, 16, 24),
+           (23, 24, 17), (8, 8), (12, 12), (16, 16), (24, 24), (32, 32), (5, 7), (9, 11), (13, 16), (20, 17), (25, 15),
+           (31, 20)]
+
+
+@pytest.mark.parametrize("Np", PWAVE32, ids=str)
+def test_fp32_waves_of_k_pwave(pk, Np):
+    print(f"[k_pwave FP32] p {Np}", flush=True)
+    w = wl.workload("three_mode_24", Nq=[5, 6, 5], Np=list(Np), K=1)
+    plan = pk.kernel_plan(pk.params_from_workload(w, precision=1, batch=2))
+    assert plan["branches"] == "k_pwave"
+    check_waves(pk, w)
+
+
+@pytest.mark.parametrize("Nq", HWAVE32, ids=str)
+def test_fp32_waves_of_k_hwave(pk, Nq):
+    print(f"[k_hwave FP32] q {Nq}", flush=True)
+    M = len(Nq)
+    w = wl.workload({2: "two_mode_32", 3: "three_mode_24"}[M], Nq=list(Nq), Np=[3, 2, 2][:M], K=2, basis="hermite")
+    plan = pk.kernel_plan(pk.params_from_workload(w, precision=1, batch=2))
+    assert plan["branches"] == "k_hwave"
+    check_waves(pk, w)
+
+
+# k_pblock for one mode (k_one switched off), with its line solves by lane pairs and by lanes
+@pytest.mark.parametrize("split", ["0", "1"])
+@pytest.mark.parametrize("Nq,Np", [(9, 12), (12, 24), (10, 48), (7, 31)])
+def test_one_mode_k_pblock(pk, monkeypatch, Nq, Np, split):
+    monkeypatch.setenv("CHFPE_ONE", "0")
+    monkeypatch.setenv("CHFPE_TUNE_PB_SPLIT", split)
+    print(f"[k_pblock] one mode {Nq} x {Np} split {split}", flush=True)
+    w = wl.workload("one_mode_48", Nq=[Nq], Np=[Np], K=2)
+    p = pk.params_from_workload(w)
+    assert pk.kernel_plan(p)["state"] == "k_pblock" and not pk.kernel_plan(p)["one"]
+    W = grid_state(w, 7)
+    with pk.Solver(p) as s:
+        s.set_state(W)
+        s.propagate(2, 0.002)
+        e_rk4 = rel_l2(s.get_state(), orc.rk4(w, W, 2, 0.002))
+        s.set_state(W)
+        s.perturb(ops(1))
+        e_x = rel_l2(s.get_state(), orc.perturb(w, ops(1), W))
+    print(f"    rk4 {e_rk4:.2e} perturb {e_x:.2e}", flush=True)
+    assert e_rk4 < TOL and e_x < TOL
