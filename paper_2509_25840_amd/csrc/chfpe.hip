@@ -605,17 +605,17 @@ bool use_pcube(const chfpe_ctx *c) {
   return !pblock_ok || (d.M == 3 && c->allow_pcube);
 }
 
-// One pass over all q axes (k_qcube) for cubes of 8, 12 or 16 points, whose tile
-// fits a workgroup's registers: it moves four states a stage where the two
-// passes move seven (16^6, eight FP32 states 7.3 -> 4.9 ms a stage; 12^6 FP64
-// 0.316 -> 0.238).  Ragged axes measured no gain, and a closure's weights spill
-// registers: those keep the two passes.  The p block must hold whole 16-byte
-// vectors of both types in use.
+// One pass over all q axes (k_qcube) for cubes of at most 16 points, whose tile
+// fits a workgroup's threads and registers: it moves four states a stage where the
+// two passes move seven (16^6, eight FP32 states 7.3 -> 4.9 ms a stage; 12^6 FP64
+// 0.316 -> 0.238; every size from 5 in qcube.h).  Axes of different lengths
+// measured no gain, and a closure's weights spill registers: those keep the two
+// passes.  The p block must hold whole 16-byte vectors of both types in use.
 bool use_qcube(const chfpe_ctx *c, long long nbat) {
   const Derived &d = c->d;
   const int n = d.Nq[0], vec = d.prec == CHFPE_FP32 ? 4 : 2;
   const int run = qcube_c(sizeof(double));  // the shorter run: more tasks
-  return c->allow_qcube && (n == 8 || n == 12 || n == 16) && d.Nq[1] == n && d.Nq[2] == n && d.P % vec == 0 &&
+  return c->allow_qcube && n <= 16 && d.Nq[1] == n && d.Nq[2] == n && d.P % vec == 0 &&
          grid_items((long long)d.ne * ((d.P + run - 1) / run) * nbat, n * n * kQcParts) <= kMaxGridItems;
 }
 

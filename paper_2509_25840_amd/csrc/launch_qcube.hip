@@ -19,11 +19,13 @@ void launch_qcube_n(chfpe_ctx *c, const Batch &b, const T *X, const T *Tacc, con
 
 template <typename T>
 void launch_qcube(chfpe_ctx *c, const Batch &b, const T *X, const T *Tacc, const T *y, T *xo, double cst, int epi) {
+#define CHFPE_QC(N) case N: launch_qcube_n<T, N>(c, b, X, Tacc, y, xo, cst, epi); break;
   switch (c->d.Nq[0]) {
-    case 8: launch_qcube_n<T, 8>(c, b, X, Tacc, y, xo, cst, epi); break;
-    case 12: launch_qcube_n<T, 12>(c, b, X, Tacc, y, xo, cst, epi); break;
+    CHFPE_QC(5) CHFPE_QC(6) CHFPE_QC(7) CHFPE_QC(8) CHFPE_QC(9) CHFPE_QC(10)
+    CHFPE_QC(11) CHFPE_QC(12) CHFPE_QC(13) CHFPE_QC(14) CHFPE_QC(15)
     default: launch_qcube_n<T, 16>(c, b, X, Tacc, y, xo, cst, epi); break;
   }
+#undef CHFPE_QC
 }
 
 template void launch_qcube<double>(chfpe_ctx *, const Batch &, const double *, const double *, const double *, double *,

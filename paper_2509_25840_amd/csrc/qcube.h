@@ -14,7 +14,10 @@
 // 0.316 -> 0.238 ms, FP32 (8 states) 1.32 -> 0.88 ms.  It reaches 3.8 (FP64) and
 // 4.4 TB/s: a run's 64-byte rows halve the use of a cache line per request, and
 // one workgroup of 16 waves (two of nine at 12 points) alternates between the
-// planes' rounds and the streaming at the end.
+// planes' rounds and the streaming at the end.  Whole RK4 steps with the two
+// passes and with this, 12^3 p points, four elements, FP64 and four FP32 states: 5^3 109
+// and 72 us, 177 and 109; 7^3 167 132, 304 225; 10^3 384 304, 844 762; 13^3 890
+// 830, 2064 1671; 15^3 1417 1383, 3126 2530; 16^3 1729 1660, 3783 3090.
 #pragma once
 
 #include "wave.h"
@@ -28,9 +31,9 @@ struct QCube {
 
 constexpr int kQcParts = 4;  // 16-byte parts of a run
 constexpr int qcube_c(const int tsize) { return kQcParts * 16 / tsize; }
-// Planes of a round: the q_1 rows of 16-point axes take 64 of the 128 registers
-// a thread of 16 waves has.
-constexpr int qcube_planes(const int nb) { return nb >= 16 ? 2 : 4; }
+// Planes of a round (the last one takes what is left): the q_1 rows of 14 to 16
+// points take most of the 128 registers a thread of 13 to 16 waves has.
+constexpr int qcube_planes(const int nb) { return nb >= 14 ? 2 : 4; }
 // Rows of the LDS tiles: c values per point and a pad of one point, so that
 // rows start in different banks.
 __host__ __device__ constexpr int qcube_row(const int n, const int c) { return (n + 1) * c; }
@@ -38,7 +41,7 @@ constexpr size_t qcube_lds_vals(const int nb, const int c) {
   return (size_t)2 * qcube_planes(nb) * nb * qcube_row(nb, c) + 3 * (size_t)c;
 }
 
-// T: type of the states and of the arithmetic.  NB: points of every q axis.
+// T: type of the states and of the arithmetic.  NB: points of every q axis (5 to 16).
 // epi: the stage update (an Epi, uniform).
 template <typename T, int NB>
 __global__ void __launch_bounds__(NB * NB * kQcParts)
@@ -98,6 +101,7 @@ k_qcube(const Geom g, const Tabs tb, const QCube qc, const T *__restrict__ X, co
     const int i0 = r * PR;
 #pragma unroll
     for (int k = 0; k < PR; ++k) {
+      if (i0 + k >= NB) continue;
       *reinterpret_cast<Vec<T, V> *>(mineA + k * slot) = cur[k];
       *reinterpret_cast<Vec<T, V> *>(mineB + k * slot) = cur[k];
       const int i = i0 + k;
@@ -112,11 +116,13 @@ k_qcube(const Geom g, const Tabs tb, const QCube qc, const T *__restrict__ X, co
     }
     if (r + 1 < NR) {  // in flight during the line solves
 #pragma unroll
-      for (int k = 0; k < PR; ++k) cur[k] = get(Xe, at(i0 + PR + k));
+      for (int k = 0; k < PR; ++k)
+        if (i0 + PR + k < NB) cur[k] = get(Xe, at(i0 + PR + k));
     }
     __syncthreads();
     // q_2 lines of A (fixed plane, q_3, p), q_3 lines of B (fixed plane, q_2, p)
-    constexpr int per = NB * C, nA = PR * per;  // lines of a plane and of a field
+    constexpr int per = NB * C;  // lines of a plane
+    const int nA = min(PR, NB - i0) * per;  // and of a field
     for (int l = tid; l < 2 * nA; l += blockDim.x) {
       const int lb = l < nA ? l : l - nA, k = lb / per;
       T *G = (l < nA ? A : B) + k * slot + (lb - k * per);
@@ -128,7 +134,8 @@ k_qcube(const Geom g, const Tabs tb, const QCube qc, const T *__restrict__ X, co
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < PR; ++k) {
-      const int i = i0 + k;
+      const int i = i0 + k < NB ? i0 + k : 0;
+      if (i0 + k >= NB) continue;
       const Vec<T, V> a = *reinterpret_cast<const Vec<T, V> *>(mineA + k * slot);
       const Vec<T, V> b = *reinterpret_cast<const Vec<T, V> *>(mineB + k * slot);
 #pragma unroll
@@ -143,7 +150,7 @@ k_qcube(const Geom g, const Tabs tb, const QCube qc, const T *__restrict__ X, co
 #pragma unroll
     for (int k = 0; k < PR; ++k) {
       const int j = i0 + k - 2;
-      if (j < 0) continue;
+      if (j < 0 || j >= NB - 2) continue;
 #pragma unroll
       for (int v = 0; v < V; ++v)
         ln[j >= 0 ? j : 0][v] = j == 0 ? ln[0][v]
@@ -167,7 +174,7 @@ k_qcube(const Geom g, const Tabs tb, const QCube qc, const T *__restrict__ X, co
   const T *Te = Tacc + eb;
   T *Oe = xo + eb;
   const T *Be = epi == EPI_H1 ? Xe : epi == EPI_H2 ? y + eb : Oe;
-  constexpr int GE = NB >= 16 ? 2 : 4;  // rows of loads issued one group ahead
+  constexpr int GE = NB >= 14 ? 2 : 4;  // rows of loads issued one group ahead
   T x[V];
 #pragma unroll
   for (int v = 0; v < V; ++v) x[v] = T(0);
@@ -175,6 +182,7 @@ k_qcube(const Geom g, const Tabs tb, const QCube qc, const T *__restrict__ X, co
   auto load_e = [&](const int j0, Vec<T, V> (&t)[GE], Vec<T, V> (&b)[GE]) {  // rows j0, j0 - 1, ...
 #pragma unroll
     for (int k = 0; k < GE; ++k) {
+      if (j0 - k < 0) continue;
       const uint32_t o = at(j0 - k);
       t[k] = get(Te, o);
       b[k] = epi == EPI_OUT ? Vec<T, V>{} : get(Be, o);
@@ -186,7 +194,8 @@ k_qcube(const Geom g, const Tabs tb, const QCube qc, const T *__restrict__ X, co
     if (j0 >= GE) load_e(j0 - GE, nt, nb);
 #pragma unroll
     for (int k = 0; k < GE; ++k) {
-      const int j = j0 - k;
+      const int j = j0 - k >= 0 ? j0 - k : 0;
+      if (j0 - k < 0) continue;
       Vec<T, V> o;
 #pragma unroll
       for (int v = 0; v < V; ++v) {

@@ -190,3 +190,25 @@ def test_one_mode_k_pblock(pk, monkeypatch, Nq, Np, split):
         e_x = rel_l2(s.get_state(), orc.perturb(w, ops(1), W))
     print(f"    rk4 {e_rk4:.2e} perturb {e_x:.2e}", flush=True)
     assert e_rk4 < TOL and e_x < TOL
+
+
+# q cubes whose planes fill the rounds of k_qcube and leave a partial last one, with
+# p blocks that end in a whole and in a partial run of 64 bytes
+@pytest.mark.parametrize("Np", [(8, 8, 8), (6, 7, 10)], ids=str)
+@pytest.mark.parametrize("N", range(5, 16))
+def test_q_cubes(pk, N, Np):
+    print(f"[k_qcube] q {N} p {Np}", flush=True)
+    w = wl.workload("three_mode_24", Nq=[N] * 3, Np=list(Np), K=1)
+    p = pk.params_from_workload(w)
+    assert pk.kernel_plan(p)["q"] == "k_qcube"
+    W = grid_state(w, 5)
+    with pk.Solver(p) as s:
+        s.set_state(W)
+        s.rhs()
+        e_rhs = rel_l2(s.get_state(), orc.rhs(w, W))
+        s.set_state(W)
+        s.propagate(2, 0.002)
+        e_rk4 = rel_l2(s.get_state(), orc.rk4(w, W, 2, 0.002))
+    print(f"    rhs {e_rhs:.2e} rk4 {e_rk4:.2e}", flush=True)
+    assert e_rhs < TOL and e_rk4 < TOL
+    check_waves(pk, w)

@@ -36,13 +36,15 @@ def test_two_modes(plan, Np, K):
     assert plan(2, (5, 7), Np, K, CHFPE_PWAVE2=0)["state"] in ("k_pblock", "k_pcube")
 
 
-@pytest.mark.parametrize("N", [8, 12, 16])
+@pytest.mark.parametrize("N", range(5, 17))
 def test_three_mode_q_cubes(plan, N):
     for Np, prec in (((8, 8, 8), 0), ((6, 7, 10), 1), ((5, 5, 12), 1)):
         got = plan(3, [N] * 3, Np, precision=prec, batch=2)
         assert got["q"] == "k_qcube" and got["q_closure"] == ("" if prec else "k_qpass")
         assert plan(3, [N] * 3, Np, precision=prec, batch=2, CHFPE_QCUBE=0)["q"] == "k_qpass"
     assert plan(3, [N] * 3, (5, 5, 7))["q"] == "k_qpass"  # 175 p points: no whole 16-byte vectors
+    assert plan(3, [N, N, N + 1], (8, 8, 8))["q"] == "k_qpass"
+    assert plan(3, [17] * 3, (8, 8, 8))["q"] == "k_qpass"
 
 
 # (p axes, FP64 state, FP32 branches, FP64 state with a closure): planes on either
