@@ -357,7 +357,8 @@ int chfpe_tile_config(const chfpe_ctx *ctx, int32_t *out, int32_t n);
  * out[2] for an FP64 state with a closure (0 where chfpe_set_closure refuses),
  * out[3] the q side (1 k_qpass, 2 k_qcube; 0 Hermite basis), out[4] the q side
  * with a closure (0 as out[2]), out[5] 1 where one-mode propagations run whole
- * in k_one.  Writes min(n, 6) values and returns that count; EINVAL where
+ * in k_one, out[6] run positions per tile of a k_qpass over two q axes (0: none
+ * such).  Writes min(n, 7) values and returns that count; EINVAL where
  * chfpe_setup refuses the parameters. */
 int chfpe_kernel_plan(const chfpe_params *p, int32_t *out, int32_t n);
 

@@ -194,13 +194,13 @@ KERNELS = ("", "k_pblock", "k_pcube", "k_pcube_s", "k_pwave", "k_pwave2", "k_hcu
 
 def kernel_plan(p: Params) -> dict:
     """chfpe_kernel_plan as a dict of kernel names ("" where nothing runs)."""
-    out = (ctypes.c_int32 * 6)()
-    k = lib().chfpe_kernel_plan(ctypes.byref(p), out, 6)
+    out = (ctypes.c_int32 * 7)()
+    k = lib().chfpe_kernel_plan(ctypes.byref(p), out, 7)
     if k < 0:
         raise ChfpeError(k, lib().chfpe_last_error(None).decode())
     q = ("", "k_qpass", "k_qcube")
     return {"state": KERNELS[out[0]], "branches": KERNELS[out[1]], "closure": KERNELS[out[2]], "q": q[out[3]],
-            "q_closure": q[out[4]], "one": bool(out[5])}
+            "q_closure": q[out[4]], "one": bool(out[5]), "q_positions": int(out[6])}
 
 
 def stream_copy(dst, src, nbytes: int, stream=None) -> None:

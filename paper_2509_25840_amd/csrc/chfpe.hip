@@ -561,8 +561,9 @@ void plan_two(chfpe_ctx *c, int a, int b, int run, std::vector<int> rest, QPass 
   // a stage launch against 74).
   if (c->tune_q_pc <= 0 && pc == 16 && out.pc == pc) {
     // (1) A launch of a few tasks per CU ends with CUs idle while others do one
-    // task more; narrower tasks where they even that out (24^4, one state: 360
-    // tasks over 256 CUs, 26.5 us a stage launch, 720 tasks 21.5 us).
+    // task more; narrower tasks where they even that out.  RK4 steps of two modes,
+    // p 24 x 24, ten elements: 360 tasks over 256 CUs or 720, q 8^2 48.0 and 46.8
+    // us, 13^2 80.9 78.2, 16^2 88.9 89.0, 20^2 144 117, 24^2 150 130, 32^2 225 212.
     auto even = [&](long long tasks) {  // share of the CUs' time in use, a task each at a time
       return (double)tasks / (double)((tasks + kCUs - 1) / kCUs * kCUs);
     };
@@ -574,9 +575,15 @@ void plan_two(chfpe_ctx *c, int a, int b, int run, std::vector<int> rest, QPass 
     // 0.61 ms, 22 x 20 1.01 -> 0.77, 20^2 FP32 1.28 -> 1.14, 26 x 30 0.251 ->
     // 0.236; two modes of 18 x 22, 16 states, 0.230 -> 0.184, 28 x 30 0.595 ->
     // 0.583.  Shorter ones lose (13 x 15 0.121 -> 0.135), and full ones: 32^2 4.03
-    // -> 4.34, 24^2 FP32 2.4 -> 2.8; 24^2 FP64 gains 0 to 10%, left with FP32.
+    // -> 4.34, 24^2 FP32 2.4 -> 2.8; 24^2 FP64 gains 0 to 10%, left with FP32.  RK4
+    // steps of three modes, q cubes of 17 to 30, p 6^3 and 8^3: 2 to 24% less.
+    // But not where it turns one round of tasks into two: steps of two modes, p 16 x
+    // 16, ten elements, 160 tasks or 320, q 18^2 80.9 and 83.5 us, 20^2 86.4 90.9, 25^2
+    // 113 122, 30^2 124 138 (p 10 x 10, 70 tasks or 130: 77.3 71.5, 81.1 75.4, 107
+    // 98.6, 123 113).
     const int fill = nmax_bucket(std::max(Na, Nb));
-    const bool part = b < d.M && (fill == 24 || fill == 32) && (Na != fill || Nb != fill);
+    const bool part = b < d.M && (fill == 24 || fill == 32) && (Na != fill || Nb != fill) &&
+                      (out.ntasks * nbat > kCUs || half.ntasks * nbat <= kCUs);
     // (its launch over every state must fit one dispatch too: threads come in whole
     // waves, so that two half-width tasks can have more than a wide one)
     const int half_thr = (std::max(Na, Nb) * half.pc + 63) / 64 * 64;
@@ -1628,13 +1635,14 @@ int chfpe_kernel_plan(const chfpe_params *p, int32_t *out, int32_t n) {
   for (int s = 0; s < d.M; ++s) clos = clos && d.Nq[s] <= 16 && d.Np[s] <= 16;
   const Launch &ln = c->ln;
   const size_t bsize = d.prec == CHFPE_FP32 ? sizeof(float) : sizeof(double);
-  const int32_t v[6] = {p_kernel(c.get(), 1, sizeof(double), false),
+  const int32_t v[7] = {p_kernel(c.get(), 1, sizeof(double), false),
                         d.batched ? p_kernel(c.get(), d.B, bsize, false) : 0,
                         clos ? p_kernel(c.get(), 1, sizeof(double), true) : 0,
                         d.hermite ? 0 : ln.qcube ? 2 : 1,
                         clos ? 1 : 0,
-                        ln.one ? 1 : 0};
-  const int k = std::min<int>(n, 6);
+                        ln.one ? 1 : 0,
+                        d.hermite ? 0 : ln.has_qa ? ln.qa.pc : ln.qf_two ? ln.qf.pc : 0};
+  const int k = std::min<int>(n, 7);
   for (int i = 0; i < k; ++i) out[i] = v[i];
   return k;
 }

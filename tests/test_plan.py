@@ -97,6 +97,15 @@ def test_two_mode_waves_of_small_planes(plan, Np, prec, batch, branches):
     assert (got["state"], got["branches"]) == ("k_pwave2", branches)
 
 
+@pytest.mark.parametrize("Nq,Np,K,prec,batch,positions", [
+    ((30, 30), (16, 16), 3, 0, 0, 16), ((30, 30), (10, 10), 3, 0, 0, 8), ((30, 30), (24, 24), 3, 0, 0, 8),
+    ((18, 22), (16, 16), 3, 0, 16, 8), ((32, 32), (16, 16), 3, 0, 0, 16), ((32, 32), (24, 24), 3, 0, 0, 8),
+    ((32, 32), (16, 16), 3, 0, 64, 16), ((13, 15), (10, 10), 3, 0, 0, 16), ((24, 24), (24, 24), 3, 0, 0, 8),
+    ((8, 18, 17), (8, 8, 8), 1, 1, 2, 8), ((8, 12, 12), (16, 16, 16), 1, 1, 4, 16)])
+def test_width_of_two_axis_q_tiles(plan, Nq, Np, K, prec, batch, positions):
+    assert plan(len(Nq), Nq, Np, K, precision=prec, batch=batch)["q_positions"] == positions
+
+
 def test_one_mode(plan):
     cases = next(m for m in test_gpu_one.test_steps_and_response_match_the_oracle.pytestmark if m.name == "parametrize")
     for Nq, Np, K in cases.args[1]:
