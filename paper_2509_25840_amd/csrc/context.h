@@ -207,12 +207,13 @@ inline int pwave_nw(const PCube &p, int nb) {
 //   16 x 10 x 10 282  287,  565  534    13 x 11 x 11   277  275,  563  514
 //   12 x 8 x 8   196  200,  315  343    12 x 9 x 9     210  220,  418  394
 //   5 x 5 x 13   137  131,  251  208    8 x 5 x 5      123  103,  182  146
+//   5 x 5 x 9    114  116,  169  178    5 x 7 x 9      127  122,  191  189
 // and with a closure 16 x 8 x 8 269 298, 16 x 9 x 9 380 329, 12 x 10 x 10 269
 // 281, 9 x 7 x 13 227 245, 5 x 11 x 13 287 237.
 inline bool pwave_pays(int nb, int n1, int plane, size_t tsize, bool clos) {
   if (nb <= 8) return true;
   if (clos) return plane > (nb == 16 && n1 > 12 ? 64 : 100);
-  if (nb <= 16) return plane > (tsize == 8 && n1 > 8 ? 90 : 64);
+  if (nb <= 16) return plane > (tsize == 4 ? 64 : n1 > 8 ? 90 : 48);
   return plane > (tsize == 8 ? (n1 > 8 ? 200 : 128) : (n1 > 8 ? 128 : 96));
 }
 // The same for three-mode k_hwave and k_hcube, by the q cube: steps of 4 x 5 x 4

@@ -55,7 +55,8 @@ THREE = [((24, 5, 5), "k_pcube", "k_pcube", ""), ((24, 13, 13), "k_pcube", "k_pw
          ((5, 7, 20), "k_pwave", "k_pwave", ""), ((16, 8, 8), "k_pcube_s", "k_pcube_s", "k_pcube"),
          ((16, 9, 9), "k_pcube_s", "k_pwave", "k_pwave"), ((13, 11, 11), "k_pwave", "k_pwave", "k_pwave"),
          ((12, 8, 8), "k_pcube_s", "k_pcube_s", "k_pcube"), ((12, 10, 10), "k_pwave", "k_pwave", "k_pcube"), ((12, 10, 9), "k_pcube_s", "k_pwave", "k_pcube"),
-         ((5, 5, 13), "k_pwave", "k_pwave", "k_pcube"), ((8, 5, 5), "k_pwave", "k_pwave", "k_pwave"),
+         ((5, 5, 13), "k_pwave", "k_pwave", "k_pcube"), ((5, 5, 9), "k_pcube_s", "k_pcube_s", "k_pcube"),
+         ((5, 6, 9), "k_pwave", "k_pcube_s", "k_pcube"), ((8, 5, 5), "k_pwave", "k_pwave", "k_pwave"),
          ((12, 12, 12), "k_pwave", "k_pwave", "k_pwave"), ((8, 5, 26), "k_pcube_s", "k_pcube_s", ""),
          ((16, 26, 9), "k_pcube_s", "k_pcube_s", ""), ((20, 7, 25), "k_pcube", "k_pcube", "")]
 
