@@ -2341,12 +2341,14 @@ int chfpe_closure_train(const float *feat, int32_t rows, int32_t n_groups, const
   if (group_start[0] != 0 || group_start[n_groups] != rows) return fail_g(CHFPE_EINVAL, "groups must cover the rows");
   std::vector<ClosGroup> groups(n_groups);
   long long gtot = 0;
+  int pmax = 0;  // of the largest group
   for (int q = 0; q < n_groups; ++q) {
     const int i0 = group_start[q], P = group_start[q + 1] - i0;
     if (P < 1) return fail_g(CHFPE_EINVAL, "empty group");
     if (!(ct[2 * q + 1] > 0.0)) return fail_g(CHFPE_EINVAL, "group target norm must be positive");
     groups[q] = ClosGroup{gtot, i0, P, ct[2 * q], ct[2 * q + 1]};
     gtot += (long long)P * P;
+    pmax = std::max(pmax, P);
   }
   hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
   const int prows = (rows + 15) / 16 * 16;  // whole tiles
@@ -2379,7 +2381,8 @@ int chfpe_closure_train(const float *feat, int32_t rows, int32_t n_groups, const
   if (!up(dgroups, groups.data(), n_groups * sizeof(ClosGroup)) || !up(dG, G, gtot * sizeof(double)) ||
       !up(db, b, rows * sizeof(double)) || !up(dnet, &host, sizeof host))
     return fail_g(CHFPE_EDEVICE, "closure train upload");
-  hipLaunchKernelGGL(k_transpose_groups, dim3(n_groups), dim3(256), 0, st, dG, dgroups);
+  const int share = (int)std::min(64LL, ((long long)pmax * pmax + 16383) / 16384);
+  hipLaunchKernelGGL(k_transpose_groups, dim3(n_groups, share), dim3(256), 0, st, dG, dgroups);
   hipLaunchKernelGGL(k_transpose_features, dim3((prows * kClosFeat + 255) / 256), dim3(256), 0, st, dfeat, dfeatT,
                      (int)rows);
   for (int step = 0; step <= n_steps; ++step) {

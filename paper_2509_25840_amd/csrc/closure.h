@@ -474,12 +474,13 @@ struct ClosGroup {
   double c, t;
 };
 
-// Transposes every group's P x P matrix in place (one workgroup per group), so
-// that the rows of a group read consecutive values.
+// Transposes every group's P x P matrix in place (blockIdx.y shares a large one
+// out), so that the rows of a group read consecutive values.
 __global__ void __launch_bounds__(256)
 k_transpose_groups(double *__restrict__ G, const ClosGroup *__restrict__ groups) {
   const ClosGroup q = groups[blockIdx.x];
-  for (long long v = threadIdx.x; v < (long long)q.P * q.P; v += blockDim.x) {
+  const long long step = (long long)gridDim.y * blockDim.x;
+  for (long long v = (long long)blockIdx.y * blockDim.x + threadIdx.x; v < (long long)q.P * q.P; v += step) {
     const long long f = v / q.P, e = v - f * q.P;
     if (e <= f) continue;  // each pair once
     const long long a = q.g + v, b = q.g + e * q.P + f;

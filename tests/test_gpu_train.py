@@ -71,7 +71,7 @@ def test_training_steps_match_the_oracle(pk, sizes):
 def test_rows_of_g_are_read_as_rows(pk):
     """G need not be symmetric: the gradient of a row takes that row of G."""
     rng = np.random.default_rng(4)
-    sizes = [17, 5, 30]
+    sizes = [17, 5, 30, 1, 150]  # (150 x 150: two workgroups transpose it)
     start = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
     feat = cl.bf16(rng.normal(size=(int(start[-1]), 16))).astype(np.float32)
     groups = [(np.arange(start[q], start[q + 1]), rng.normal(size=(P, P)), rng.normal(size=P), 1.0, 2.0)
