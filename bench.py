@@ -270,6 +270,8 @@ def _kind_of(short: str, grid: int, min_grid: dict):
         kind = "hcube_rk4"  # <T, NB, NVR, MM>: the stage update is an argument, one kind for all
     elif fam == "k_hperturb":
         kind = "perturb"
+    elif fam == "k_one":
+        kind = "one_propagation"
     elif fam == "k_reduce_w0":
         kind = "observe"
     else:
@@ -349,7 +351,8 @@ def summarise_counters(args, kern_cmd: str) -> None:
         passes.append(names)
         for r in rows:
             s = _short_name(r["Kernel_Name"])
-            if not s.startswith(("k_pcube", "k_pwave", "k_qpass", "k_qcube", "k_pblock", "k_hcube", "k_hwave")):
+            if not s.startswith(("k_pcube", "k_pwave", "k_qpass", "k_qcube", "k_pblock", "k_hcube", "k_hwave",
+                                  "k_one")):
                 continue
             key = (s, _grid(r))
             per.setdefault(key, {})

@@ -11,7 +11,7 @@
 // generator, which classical RK4 equals for a linear time-independent
 // system, in nested form (four stages, see Epi in kernels.h).  A stage is one
 // p-axis launch (k_pwave2 for two modes, k_pwave for three, k_pblock or k_pcube
-// where those do not fit) followed by k_qcube, or by one or two k_qpass launches,
+// where those do not fit or pay) followed by k_qcube, or by one or two k_qpass launches,
 // the last of which applies the stage update.  One mode runs whole propagations
 // in k_one; a Hermite stage is one launch of k_hwave or k_hcube.
 #include <hip/hip_runtime.h>

@@ -1036,7 +1036,8 @@ k_pcube(const Geom g, const Tabs tb, const PCube pc, const T *__restrict__ X, TO
 // of the block), so the LDS holds only a round's two planes and the first ND
 // forward results d_j of every line (the rest stay in registers); the back
 // substitution then writes t.  Plain stencils only (a closure keeps k_pcube).
-// It is left to what k_pwave does not take: a p axis above 24 points.
+// It is left to what k_pwave does not take: a p axis above 24 points, or small
+// planes.
 
 // Task constants of k_pcube_s in LDS: slots of the groups below (three
 // modes each) and the damping, then the p_2 and p_3 grids.
