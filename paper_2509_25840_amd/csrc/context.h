@@ -196,38 +196,47 @@ inline int pwave_nw(const PCube &p, int nb) {
 // lines in the nb bucket; below, k_pcube (p_1 axes up to 16 points and no
 // closure: k_pcube_s).  A wave goes through its planes one by one, with all nb
 // steps of a line solve and all vectors of its variant however few lines and
-// points they have; k_pcube's cost follows the points in waves of 64.  RK4
-// steps at 504 q points and four elements, k_pcube[_s] and k_pwave, FP64 and
-// four FP32 states, in us:
-//   24 x 5 x 5   226  506,  392  757    24 x 13 x 13   802  794, 1866 1482
-//   24 x 10 x 10 505  652, 1038 1081    24 x 16 x 16  1112  986, 2461 2031
-//   24 x 12 x 11 682  727, 1620 1282    17 x 14 x 14   687  728, 1712 1426
-//   5 x 6 x 20   164  197,  326  312    5 x 7 x 20     230  225,  425  350
-//   16 x 8 x 8   223  233,  370  420    16 x 9 x 9     254  262,  500  489
-//   16 x 10 x 10 282  287,  565  534    13 x 11 x 11   277  275,  563  514
-//   12 x 8 x 8   196  200,  315  343    12 x 9 x 9     210  220,  418  394
-//   5 x 5 x 13   137  131,  251  208    8 x 5 x 5      123  103,  182  146
-//   5 x 5 x 9    114  116,  169  178    5 x 7 x 9      127  122,  191  189
+// points they have, and n1 sets how many workgroups share a CU's eight waves
+// (24-point lines, 13 to 16 planes: one of five or six waves); k_pcube's cost
+// follows the points in waves of 64.  RK4 steps at 504 q points and four elements,
+// k_pcube[_s] and k_pwave, FP64 and four FP32 states, in us:
+//   24 x 5 x 5    226  506,  392  757    24 x 12 x 12  717  747, 1701 1335
+//   24 x 9 x 18   781  777, 1816 1436    24 x 16 x 16 1112  986, 2461 2031
+//   17 x 13 x 17  711  756, 1814 1516    17 x 10 x 24  788  780, 1968 1576
+//   16 x 8 x 17   415  571,  809 1114    16 x 15 x 17  605  731, 1417 1533
+//   16 x 16 x 17  941  822, 1972 2194    10 x 10 x 17  343  376,  678  651
+//   8 x 15 x 17   388  424,  847  682    8 x 16 x 17   566  460, 1277  795
+//   5 x 6 x 18    157  195,  303  300    5 x 8 x 17    221  225,  402  345
+//   16 x 8 x 8    223  233,  370  420    16 x 9 x 9    254  262,  500  489
+//   16 x 10 x 10  282  287,  565  534    13 x 11 x 11  277  275,  563  514
+//   12 x 8 x 8    196  200,  315  343    12 x 9 x 9    210  220,  418  394
+//   8 x 7 x 9     157  149,  250  240    8 x 5 x 5     123  103,  182  146
+//   5 x 5 x 9     114  116,  169  178    5 x 7 x 9     127  122,  191  189
 // and with a closure 16 x 8 x 8 269 298, 16 x 9 x 9 380 329, 12 x 10 x 10 269
 // 281, 9 x 7 x 13 227 245, 5 x 11 x 13 287 237.
 inline bool pwave_pays(int nb, int n1, int plane, size_t tsize, bool clos) {
   if (nb <= 8) return true;
   if (clos) return plane > (nb == 16 && n1 > 12 ? 64 : 100);
-  if (nb <= 16) return plane > (tsize == 4 ? 64 : n1 > 8 ? 90 : 48);
-  return plane > (tsize == 8 ? (n1 > 8 ? 200 : 128) : (n1 > 8 ? 128 : 96));
+  if (nb <= 16) return plane > (n1 <= 8 ? 48 : tsize == 4 ? 64 : nb <= 12 ? 110 : 90);
+  if (tsize == 4) return plane > (n1 <= 6 ? 96 : n1 > 12 && n1 <= 16 ? 400 : 128);
+  return plane > (n1 <= 6 ? 128 : n1 <= 16 ? 256 : n1 < 24 ? 224 : 150);
 }
 // The same for three-mode k_hwave and k_hcube, by the q cube: steps of 4 x 5 x 4
 // functions and ten elements, k_hcube and k_hwave, FP64 and four FP32 states:
-//   24 x 5 x 5   214  410,  249  746    24 x 13 x 13   328  445,  869  860
-//   24 x 16 x 16 684  456, 1028  917    17 x 14 x 14   467  384,  707  840
-//   12 x 10 x 20 204  229,  479  349    5 x 13 x 20    276  124,  358  224
-//   5 x 8 x 20   104  111,  188  199    16 x 7 x 7     174  172,  203  236
-//   13 x 8 x 8   161  167,  185  220    16 x 9 x 9     190  179,  339  248
-//   12 x 5 x 5   115   99,  137  155    12 x 8 x 8     145  102,  169  163
+//   24 x 5 x 5    214  410,  249  746    24 x 13 x 13  328  445,  869  860
+//   24 x 11 x 18  625  448,  934  890    17 x 14 x 14  467  384,  707  840
+//   17 x 15 x 17  488  385,  736  859    17 x 16 x 17  973  404, 1361  899
+//   16 x 8 x 17   227  345,  429  722    16 x 15 x 17  276  365,  646  804
+//   12 x 10 x 20  204  229,  479  349    12 x 8 x 20   193  222,  356  334
+//   10 x 9 x 18   159  207,  294  319    5 x 13 x 20   276  124,  358  224
+//   5 x 8 x 20    104  111,  188  199    16 x 7 x 7    174  172,  203  236
+//   13 x 8 x 8    161  167,  185  220    16 x 9 x 9    190  179,  339  248
+//   12 x 5 x 5    115   99,  137  155    12 x 8 x 8    145  102,  169  163
 inline bool hwave_pays(int nb, int n1, int plane, size_t tsize) {
   if (nb <= 8) return true;
-  if (tsize == 8) return plane > (nb <= 12 ? 0 : nb <= 16 ? 48 : n1 > 16 ? 192 : 256);
-  return plane > (nb <= 12 ? 48 : nb <= 16 ? 64 : n1 > 16 ? 200 : n1 > 8 ? 128 : 160);
+  if (tsize == 8) return plane > (nb <= 12 ? 0 : nb <= 16 ? (n1 < 16 ? 64 : 48) : n1 > 16 ? 192 : 256);
+  if (nb <= 16) return plane > (nb <= 12 ? 63 : 64);
+  return plane > (n1 <= 10 ? 192 : n1 <= 12 || n1 == 24 ? 136 : 256);
 }
 // Where k_pwave2 is the faster form for a launch of `tasks` planes: a task is a
 // wave however small its plane, and once there are several waves for every slot

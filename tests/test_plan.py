@@ -49,14 +49,18 @@ def test_three_mode_q_cubes(plan, N):
 
 # (p axes, FP64 state, FP32 branches, FP64 state with a closure): planes on either
 # side of each line between k_pwave and k_pcube, and axes that only k_pcube_s takes
-THREE = [((24, 5, 5), "k_pcube", "k_pcube", ""), ((24, 13, 13), "k_pcube", "k_pwave", ""),
-         ((24, 16, 16), "k_pwave", "k_pwave", ""), ((17, 12, 10), "k_pcube", "k_pcube", ""),
+THREE = [((24, 5, 5), "k_pcube", "k_pcube", ""), ((24, 12, 12), "k_pcube", "k_pwave", ""),
+         ((24, 9, 18), "k_pwave", "k_pwave", ""), ((17, 12, 10), "k_pcube", "k_pcube", ""),
+         ((20, 13, 17), "k_pcube", "k_pwave", ""), ((20, 13, 18), "k_pwave", "k_pwave", ""),
+         ((16, 15, 17), "k_pcube_s", "k_pcube_s", ""), ((16, 16, 17), "k_pwave", "k_pcube_s", ""),
+         ((10, 10, 17), "k_pcube_s", "k_pwave", ""), ((8, 16, 17), "k_pwave", "k_pwave", ""),
          ((5, 6, 20), "k_pcube_s", "k_pwave", ""), ((5, 5, 18), "k_pcube_s", "k_pcube_s", ""),
          ((5, 7, 20), "k_pwave", "k_pwave", ""), ((16, 8, 8), "k_pcube_s", "k_pcube_s", "k_pcube"),
          ((16, 9, 9), "k_pcube_s", "k_pwave", "k_pwave"), ((13, 11, 11), "k_pwave", "k_pwave", "k_pwave"),
-         ((12, 8, 8), "k_pcube_s", "k_pcube_s", "k_pcube"), ((12, 10, 10), "k_pwave", "k_pwave", "k_pcube"), ((12, 10, 9), "k_pcube_s", "k_pwave", "k_pcube"),
+         ((12, 8, 8), "k_pcube_s", "k_pcube_s", "k_pcube"), ((12, 10, 10), "k_pcube_s", "k_pwave", "k_pcube"),
+         ((12, 11, 11), "k_pwave", "k_pwave", "k_pwave"), ((14, 9, 11), "k_pwave", "k_pwave", "k_pwave"),
          ((5, 5, 13), "k_pwave", "k_pwave", "k_pcube"), ((5, 5, 9), "k_pcube_s", "k_pcube_s", "k_pcube"),
-         ((5, 6, 9), "k_pwave", "k_pcube_s", "k_pcube"), ((8, 5, 5), "k_pwave", "k_pwave", "k_pwave"),
+         ((5, 6, 9), "k_pwave", "k_pwave", "k_pcube"), ((8, 5, 5), "k_pwave", "k_pwave", "k_pwave"),
          ((12, 12, 12), "k_pwave", "k_pwave", "k_pwave"), ((8, 5, 26), "k_pcube_s", "k_pcube_s", ""),
          ((16, 26, 9), "k_pcube_s", "k_pcube_s", ""), ((20, 7, 25), "k_pcube", "k_pcube", "")]
 
@@ -72,9 +76,11 @@ def test_three_modes(plan, Np, f64, f32, clos):
 
 
 # (q axes, FP64 state, FP32 branches): as above for k_hwave and k_hcube
-HERMITE = [((24, 5, 5), "k_hcube", "k_hcube"), ((24, 13, 13), "k_hcube", "k_hcube"), ((24, 16, 16), "k_hwave", "k_hwave"),
-           ((17, 14, 14), "k_hwave", "k_hcube"), ((12, 10, 20), "k_hcube", "k_hwave"), ((5, 13, 20), "k_hwave", "k_hwave"),
-           ((16, 7, 7), "k_hwave", "k_hcube"), ((16, 6, 6), "k_hcube", "k_hcube"), ((13, 9, 9), "k_hwave", "k_hwave"),
+HERMITE = [((24, 5, 5), "k_hcube", "k_hcube"), ((24, 13, 13), "k_hcube", "k_hwave"), ((24, 11, 18), "k_hwave", "k_hwave"),
+           ((17, 14, 14), "k_hwave", "k_hcube"), ((17, 16, 17), "k_hwave", "k_hwave"), ((16, 15, 17), "k_hcube", "k_hcube"),
+           ((16, 16, 17), "k_hwave", "k_hwave"), ((12, 10, 20), "k_hcube", "k_hwave"), ((10, 9, 18), "k_hcube", "k_hcube"),
+           ((10, 12, 18), "k_hcube", "k_hwave"), ((5, 13, 20), "k_hwave", "k_hwave"), ((16, 7, 7), "k_hwave", "k_hcube"),
+           ((16, 6, 6), "k_hcube", "k_hcube"), ((13, 8, 8), "k_hcube", "k_hcube"), ((13, 9, 9), "k_hwave", "k_hwave"),
            ((12, 5, 5), "k_hwave", "k_hcube"), ((12, 8, 8), "k_hwave", "k_hwave"), ((8, 5, 5), "k_hwave", "k_hwave"),
            ((32, 8, 9), "k_hcube", "k_hcube"), ((6, 27, 7), "k_hcube", "k_hcube"), ((40, 20), "k_hcube", "k_hcube"),
            ((33, 9), "k_hcube", "k_hcube"), ((5, 5), "k_hwave", "k_hwave"), ((32, 5), "k_hwave", "k_hwave"),
